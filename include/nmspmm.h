@@ -271,8 +271,11 @@ nm_status nm_spmm(const int8_t *X, int m, const int8_t *vals, const uint8_t *met
                   const nm_desc *desc, int32_t *Y, const float *scale, uint16_t *Yh,
                   void *ws, size_t ws_bytes, void *stream);
 
-/* nm_spmm with an explicit plan (NULL = the planner's); the plan's kind must
- * be the descriptor's kind (nm_spmm_plan returns such plans). */
+/* nm_spmm with an explicit plan; the plan's kind must be the descriptor's kind
+ * (nm_spmm_plan returns such plans), and the call runs the plan's tile.  NULL
+ * leaves the schedule to the library, like every call without a plan: it needs
+ * the workspace of the planner's plan and no more, but may run a workgroup
+ * tile that the planner does not name where that is faster. */
 nm_status nm_spmm_ex(const int8_t *X, int m, const int8_t *vals, const uint8_t *meta,
                      const nm_desc *desc, int32_t *Y, const float *scale, uint16_t *Yh,
                      void *ws, size_t ws_bytes, void *stream, const nm_plan *plan);

@@ -37,14 +37,18 @@ nm_outputs outputs_of(int32_t *Y, const float *scale, uint16_t *Yh) {
 // 2:4 fc1 on 128 x 128 tiles 125 -> 82-86 us, qkv 93 -> 65-68, fc2 84 -> 77-79,
 // proj 36 -> 32; groups of 4 or 8 rows gained less, 32 lost.  Launches with
 // fewer than 32 rows of tiles keep the row order.
-constexpr int kGroupRows = 16;
+// The wider tiles keep about the same number of tokens per group (X is read
+// once per group and XCD): 256 x 256, ViT-L qkv 2:4 fp16 54.4 us in groups of
+// 16 and 52.7-53.9 in groups of 2 to 6; 256 x 160, DeiT-B batch 128 fc2 44.4
+// and 42.3.
+int group_size(int tile_m) { return tile_m >= 256 ? 4 : tile_m >= 160 ? 6 : 16; }
 
 int64_t stored_weight_bytes(int kind, int n, int k, int n_frags, int k_steps) {
     return kind == NM_KIND_DENSE ? (int64_t)n * k
                                  : (int64_t)n_frags * k_steps * 64 * (layout_lane_vbytes(kind) + layout_lane_mbytes(kind));
 }
 
-int group_rows_for(int tiles_m) { return tiles_m >= 2 * kGroupRows ? kGroupRows : 0; }
+int group_rows_for(int tiles_m, int tile_m) { return tiles_m >= 2 * group_size(tile_m) ? group_size(tile_m) : 0; }
 
 // Whether the byte ranges [a, a + na) and [b, b + nb) intersect (a null or
 // empty range intersects nothing).
@@ -130,7 +134,7 @@ nm_status run_gemm(int kind, const int8_t *X, int m, const int8_t *A, const uint
 
     // With expand = 1 the compact weight is first expanded into the workspace
     // (after the split-K area), and the 4:2-operand or dense kernel runs on it.
-    int run_kind = kind;
+    int run_kind = kind, tile = plan.tile;
     if (plan.expand) {
         int8_t *exp = (int8_t *)ws + expand_offset(plan.split_k, m, n);
         if (launch_expand(kind, A, meta, n, k, exp, stream) != 0) return NM_ERR_HIP;
@@ -139,6 +143,13 @@ nm_status run_gemm(int kind, const int8_t *X, int m, const int8_t *A, const uint
         meta = run_kind == NM_KIND_SP42 ? (const uint8_t *)(exp + (int64_t)n_frags * k_steps * kVBlock) : nullptr;
     }
     const bool split = plan.split_k > 1;
+    int grid = plan.grid;
+    if (!forced && !split) {
+        // the schedule is ours to choose: the planner's tile or a faster one
+        tile = schedule_tile(run_kind, m, n, k, out_mode_of(o), plan.tile);
+        grid = ((n + kTiles[tile].tile_n() - 1) / kTiles[tile].tile_n()) *
+               ((m + kTiles[tile].tile_m() - 1) / kTiles[tile].tile_m());
+    }
     GemmArgs a;
     a.X = X;
     a.A = A;
@@ -155,16 +166,16 @@ nm_status run_gemm(int kind, const int8_t *X, int m, const int8_t *A, const uint
     a.k = k;
     a.k_steps = k_steps;
     a.n_frags = n_frags;
-    a.tiles_n = (n + plan.tile_n - 1) / plan.tile_n;
-    a.tiles_m = (m + plan.tile_m - 1) / plan.tile_m;
+    a.tiles_n = (n + kTiles[tile].tile_n() - 1) / kTiles[tile].tile_n();
+    a.tiles_m = (m + kTiles[tile].tile_m() - 1) / kTiles[tile].tile_m();
     a.split_k = plan.split_k;
-    a.group_rows = group_rows_for(a.tiles_m);
-    a.gemm_grid = plan.grid;
-    int grid = plan.grid;
+    a.stream_out = stream_out_for(n);
+    a.group_rows = group_rows_for(a.tiles_m, kTiles[tile].tile_m());
+    a.gemm_grid = grid;
     if (job) {
         // the job's blocks go to workgroups appended after the GEMM's, one per wave
         const nm_desc *d = job->desc;
-        const int per = tile_waves(kTiles[plan.tile]);
+        const int per = tile_waves(kTiles[tile]);
         const int64_t blocks = (int64_t)d->n_frags * d->k_steps;
         const int64_t extra = (blocks + per - 1) / per;
         if ((int64_t)grid + extra > 0x7fffffff) return NM_ERR_SHAPE;
@@ -178,7 +189,7 @@ nm_status run_gemm(int kind, const int8_t *X, int m, const int8_t *A, const uint
         a.x_k_steps = d->k_steps;
         grid += (int)extra;
     }
-    int err = launch_gemm(run_kind, plan.tile, a, grid, stream);
+    int err = launch_gemm(run_kind, tile, a, grid, stream);
     return err == 0 ? NM_OK : NM_ERR_HIP;
 }
 

@@ -67,8 +67,14 @@ constexpr TileCfg kTiles[] = {
     {1, 1, 4, 2, 3, kKSliced},   // 9:  64 ch x  32 tok, k-sliced
     {1, 1, 2, 2, 3, kKSliced},   // 10: 32 ch x  32 tok, k-sliced
     {2, 2, 4, 5, 2, kOutSplit},  // 11: 128 ch x 160 tok, 2-slot ring (long reductions, narrow outputs)
+    // Tiles that only calls without an explicit plan run on (schedule_tile):
+    {4, 2, 4, 5, 3, kOutSplit},  // 12: 256 ch x 160 tok, 8 waves (4 x 2), 3-slot ring
+    {2, 2, 4, 2, 4, kOutSplit},  // 13: 128 ch x  64 tok, 4-slot ring
+    {2, 2, 2, 4, 4, kOutSplit},  // 14:  64 ch x 128 tok, 4-slot ring
+    {2, 4, 8, 5, 2, kOutSplit},  // 15: 256 ch x 320 tok, 8 waves (2 x 4), 2-slot ring
 };
-constexpr int kNumTiles = sizeof(kTiles) / sizeof(kTiles[0]);
+constexpr int kNumSchedules = sizeof(kTiles) / sizeof(kTiles[0]);
+constexpr int kNumTiles = 12;    // tiles of explicit plans: the first of the table
 constexpr size_t kLdsPerCu = 160 * 1024;
 
 // Everything a GEMM kernel needs; passed by value as the kernel argument.
@@ -86,6 +92,7 @@ struct GemmArgs {
     int m, n, k;
     int k_steps, n_frags;
     int tiles_n, tiles_m, split_k;
+    int stream_out = 0;     // outputs stored non-temporally: bytes per element, or-ed (1, 2, 4)
     int group_rows;         // tile order: 0 row by row, else groups of this many tile rows
     // Workgroups gemm_grid .. gridDim.x - 1 of the launch do not belong to the
     // GEMM: they expand another compact weight (x_kind, blocks as in the
@@ -97,6 +104,20 @@ struct GemmArgs {
     int8_t *x_out = nullptr;
     int x_n = 0, x_k = 0, x_blocks = 0, x_k_steps = 0;
 };
+
+// Store policy of each output: non-temporal where its rows start on a 128-byte
+// line, so that every store of a tile's row writes whole lines.  Where they do
+// not, a line at the border of two tiles is written in two pieces, which L2
+// can join only if the stores go through it as usual: m 14691, n 1444, k 176
+// int32 + fp16 51.8 us non-temporal and 33.3 through L2 (87 at 4 bytes a lane),
+// m 30000, n 500, k 256 int32 20.7 and 15.1; on whole lines it is the other
+// way round (m 100352, n 512, k 128 int32 35.8 and 43).
+inline int stream_out_for(int n) {
+    int mask = 0;
+    for (int eb : {1, 2, 4})
+        if ((int64_t)n * eb % 128 == 0) mask |= eb;
+    return mask;
+}
 
 // Workspace of a plan: with split_k > 1 a fixed block of per-tile arrival
 // counters, then split_k partial [m x n] int32 tiles; then, with expand = 1,
@@ -143,5 +164,8 @@ int kind_of(const nm_desc *d);
 // Planner shared by both GEMM families.
 nm_status make_plan(int kind, int m, int n, int k, int out_mode, nm_plan *plan);
 nm_status complete_plan(int kind, int m, int n, int k, nm_plan *plan);
+// Without an explicit plan: the tile (index into kTiles, up to kNumSchedules)
+// with the least estimated time for the planner's unsplit plan.
+int schedule_tile(int kind, int m, int n, int k, int out_mode, int planned);
 
 }  // namespace nmspmm

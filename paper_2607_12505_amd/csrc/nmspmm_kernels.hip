@@ -10,31 +10,28 @@
 // Dataflow of one workgroup (4 or 8 waves) over its k range, one 128-wide
 // k-step at a time (paper Sec. 4.2: sparse handling confined to packed
 // loading, the compute stage purely matrix-instruction based):
-//   - every X byte reaches LDS through the direct-to-LDS 16-byte loads of
-//     gfx950, into a ring of NST k-step slots filled NST-1 steps ahead of the
-//     compute: the tile_m x 128 slice of X, and with it the weight slice as
-//     stored when it is already what the matrix instruction reads (the 4:2
-//     fragments of 2:4, or tile_n x 128 rows of a dense W).  Each workgroup
-//     fetches each byte once; no VGPRs are spent on staging, so the ring
-//     depth costs only LDS.  Each lane picks the source chunk that belongs at
-//     its LDS slot, so row-major slices land with their 16-byte chunks
-//     XOR-swizzled by row and the operand reads of 16 rows hit distinct banks;
-//   - compact weights (1:4, 1:8, 2:8 and the 3:8-5:8 mask layouts) are
-//     expanded on the way (Sec. 4.2): in k_gemm each wave loads its blocks of
-//     the next k-step into registers and writes them, expanded, into the slot
-//     (the 4:2 operand or swizzled dense rows); in k_gemm_ks the 1:4, 1:8 and
-//     2:8 blocks travel through the ring like X and are expanded straight into
-//     the operand registers.  k_expand does the same expansion once per call
-//     into the workspace when the planner prefers that;
+//   - X and the weight as stored (the 4:2 fragments of 2:4, the compact blocks
+//     of the other patterns, or tile_n x 128 rows of a dense W) reach LDS
+//     through the direct-to-LDS 16-byte loads of gfx950, into a ring of k-step
+//     slots filled as soon as a slot is free.  Each workgroup fetches each byte
+//     once; no VGPRs are spent on staging, so the ring depth costs only LDS.
+//     Each lane picks the source chunk that belongs at its LDS slot, so
+//     row-major slices land with their 16-byte chunks XOR-swizzled by row and
+//     the operand reads of 16 rows hit distinct banks;
 //   - the loads are issued from inline assembly and their completion is
 //     awaited explicitly (vector-memory counter, then one barrier per k-step),
 //     so the compiler does not serialise the ring with conservative waits;
-//   - each wave runs FN x FM accumulators: per k-step it reads its FN weight
-//     fragments from LDS once, then per token fragment the B operand once,
-//     reused by all FN weight fragments;
-//   - the epilogue goes back through LDS, 16 tokens at a time, so that every
-//     store instruction writes whole rows of the wave's tile: 16 lanes cover
-//     256 contiguous bytes of int32 (128 of fp16, 64 of int8) per token;
+//   - k_gemm: each wave runs FN x FM accumulators and reads every operand from
+//     LDS into registers one phase ahead of the matrix instructions that use
+//     it, across the k-step's barrier too.  A compact block is expanded (Sec.
+//     4.2) in the registers of the lane that multiplies it: 1:4, 1:8 and 2:8
+//     into the 4:2 operand, 3:8-5:8 into dense weights.  k_expand does the same
+//     expansion once per call into the workspace when the planner prefers that;
+//   - k_gemm_ks: the four waves split the k-steps instead of the tile, each
+//     with a ring of its own, and add their tiles through LDS at the end;
+//   - the epilogue packs to the output type and goes back through LDS, so that
+//     every store instruction writes whole rows of the wave's tile, 16 bytes
+//     per lane;
 //   - split-K (Sec. 4.3): every split runs the same code on its k range and
 //     stores its int32 partial tile; the last split to arrive at a tile
 //     (atomic counter) adds the partials and runs the epilogue, so merging
@@ -51,7 +48,6 @@ namespace {
 typedef int v4i __attribute__((ext_vector_type(4)));
 typedef int v8i __attribute__((ext_vector_type(8)));
 typedef float v4f __attribute__((ext_vector_type(4)));
-typedef unsigned short v4u16 __attribute__((ext_vector_type(4)));
 
 // Workgroups are dispatched round-robin over the 8 XCDs (each with its own
 // L2).  Renumber them so that consecutive logical tiles -- which share the
@@ -104,14 +100,14 @@ __device__ inline void dma4(const void *g, uint32_t lds_base) {
     asm volatile("s_mov_b32 m0, %1\n\tglobal_load_lds_dword %0, off" ::"v"(g), "s"(lds_base) : "memory", "m0");
 }
 // The same with a wave-uniform 64-bit base in SGPRs and a 32-bit per-lane
-// byte offset: no per-lane 64-bit address arithmetic.
-__device__ inline void dma16o(const void *base, uint32_t off, uint32_t lds_base) {
-    asm volatile("s_mov_b32 m0, %2\n\tglobal_load_lds_dwordx4 %0, %1" ::"v"(off), "s"(base), "s"(lds_base)
-                 : "memory", "m0");
-}
-__device__ inline void dma4o(const void *base, uint32_t off, uint32_t lds_base) {
-    asm volatile("s_mov_b32 m0, %2\n\tglobal_load_lds_dword %0, %1" ::"v"(off), "s"(base), "s"(lds_base)
-                 : "memory", "m0");
+// byte offset (no per-lane 64-bit address arithmetic), skipped unless the
+// wave-uniform `live` is positive: a scalar branch inside the statement, so
+// the surrounding schedule stays one block.
+__device__ inline void dma16o_if(const void *base, uint32_t off, uint32_t lds_base, int live) {
+    asm volatile(
+        "s_cmp_lt_i32 %3, 1\n\ts_cbranch_scc1 1f\n\ts_mov_b32 m0, %2\n\tglobal_load_lds_dwordx4 %0, %1\n1:" ::"v"(off),
+        "s"(base), "s"(lds_base), "s"(live)
+        : "m0", "scc");
 }
 
 // Wait until at most N of this wave's vector-memory operations are in flight
@@ -149,30 +145,14 @@ __device__ inline void wait_later(int later) {
     }
 }
 
-// Barrier of k-step iteration with `later` k-steps (each DMA loads per wave)
-// still allowed in flight: dispatches to the matching immediate.  The vmcnt
-// field holds at most 63; beyond that fewer loads are allowed in flight
-// (waiting longer is always safe).
-template <int L, int DMA>
-__device__ inline void wait_later_then_barrier(int later) {
-    if constexpr (L <= 0) {
-        wait_then_barrier<0>();
-    } else {
-        if (later >= L) {
-            constexpr int n = L * DMA <= 63 ? L * DMA : (63 / DMA) * DMA;
-            wait_then_barrier<n>();
-        } else {
-            wait_later_then_barrier<L - 1, DMA>(later);
-        }
-    }
-}
-
 // int8 code of a binary32 value: nearest integer (ties to even), saturated
-// to [-127, 127], NaN -> 0.
+// to [-127, 127], NaN -> 0.  v_cvt_i32_f32 itself saturates and turns NaN into
+// 0 (which a C conversion leaves undefined), so the code is five instructions.
 __device__ inline int q8(float v) {
-    if (v != v) return 0;
-    const float r = __builtin_rintf(v);
-    return (int)fminf(fmaxf(r, -127.0f), 127.0f);
+    int r;
+    asm("v_cvt_i32_f32 %0, %1" : "=v"(r) : "v"(__builtin_rintf(v)));
+    r = r < -127 ? -127 : r;
+    return r > 127 ? 127 : r;
 }
 
 // Per-channel multipliers of the epilogue outputs for 4 consecutive channels.
@@ -183,6 +163,28 @@ struct EpiScale {
 
 typedef unsigned int v2u __attribute__((ext_vector_type(2)));
 typedef unsigned int v4u __attribute__((ext_vector_type(4)));
+typedef _Float16 v2h __attribute__((ext_vector_type(2)));
+
+// 4 channels of one token as binary16 (the product rounded to binary32 first)
+// and as int8 codes.
+__device__ inline v2u pack_f16(const v4i &v, const v4f &sc) {
+    v2u h;
+#pragma unroll
+    for (int q = 0; q < 2; ++q) {
+        float lo = (float)v[2 * q] * sc[2 * q], hi = (float)v[2 * q + 1] * sc[2 * q + 1];
+        asm("" : "+v"(lo), "+v"(hi));   // no fused multiply-and-round to binary16
+        const v2h x = {(_Float16)lo, (_Float16)hi};
+        h[q] = __builtin_bit_cast(unsigned, x);
+    }
+    return h;
+}
+__device__ inline uint32_t pack_q8(const v4i &v, const v4f &qs) {
+    const uint32_t lo = __builtin_amdgcn_perm((uint32_t)q8((float)v[1] * qs[1]), (uint32_t)q8((float)v[0] * qs[0]),
+                                              0x0C0C0400u);
+    const uint32_t hi = __builtin_amdgcn_perm((uint32_t)q8((float)v[3] * qs[3]), (uint32_t)q8((float)v[2] * qs[2]),
+                                              0x0C0C0400u);
+    return __builtin_amdgcn_perm(hi, lo, 0x05040100u);
+}
 
 // Writes 4 consecutive channels of one token: int32, fp16(fp32(y) * scale)
 // and/or the int8 code q8(fp32(y) * qscale), whichever outputs are present.
@@ -198,19 +200,12 @@ __device__ inline void emit_out(const GemmArgs &a, int tok, int ch, const v4i &v
         __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(v4u, v), r, (int)(e * 4), 0, kStoreNT);
     }
     if (a.Yh) {
-        v4u16 h;
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            const _Float16 x = (_Float16)((float)v[i] * es.sc[i]);
-            h[i] = __builtin_bit_cast(unsigned short, x);
-        }
+        const v2u h = pack_f16(v, es.sc);
         const __amdgpu_buffer_rsrc_t r = __builtin_amdgcn_make_buffer_rsrc(a.Yh, 0, (int)(elems * 2), kBufferFlags);
-        __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(v2u, h), r, (int)(e * 2), 0, kStoreNT);
+        __builtin_amdgcn_raw_buffer_store_b64(h, r, (int)(e * 2), 0, kStoreNT);
     }
     if (a.Yq) {
-        uint32_t packed = 0;
-#pragma unroll
-        for (int i = 0; i < 4; ++i) packed |= (uint32_t)(q8((float)v[i] * es.qs[i]) & 0xFF) << (8 * i);
+        const uint32_t packed = pack_q8(v, es.qs);
         const __amdgpu_buffer_rsrc_t r = __builtin_amdgcn_make_buffer_rsrc(a.Yq, 0, (int)elems, kBufferFlags);
         __builtin_amdgcn_raw_buffer_store_b32(packed, r, (int)e, 0, kStoreNT);
     }
@@ -287,14 +282,14 @@ __device__ inline bool arrive_last(const GemmArgs &a, int tile, int *s_flag) {
 }
 
 // ---------------------------------------------------------------------------
-// Weight kinds.  The weight reaches LDS either as stored (DMA: the 4:2 operand
-// of 2:4, or plain rows of a dense W) or in a compact packed form that every
-// workgroup loads into registers one k-step ahead, expands, and writes to LDS
-// in the form the matrix instruction reads (paper Sec. 4.2: decoding
-// overlapped with shared-memory placement and matrix issue): the 4:2 operand
-// for 1:4, 1:8 and 2:8, a dense tile for the mask layouts of 3:8, 4:8 and 5:8.
-// (The k-sliced kernel instead stages the 1:4, 1:8 and 2:8 blocks in its ring
-// as stored and expands them into operand registers, see k_gemm_ks.)
+// Weight kinds.  The weight reaches LDS as stored: the 4:2 operand of 2:4,
+// plain rows of a dense W, or the compact blocks of the other patterns, which
+// k_gemm (and k_gemm_ks for 1:4, 1:8 and 2:8) expands in the registers of the
+// lanes that multiply them -- a lane of a block holds exactly the weights that
+// the lane feeds to the matrix instruction.  Expanding in the workgroup and
+// writing the result back to LDS instead cost an LDS round trip and a wait for
+// all loads in flight per k-step (Swin-B stage 4 fc1, 2:8, int8: 15.8 us
+// against 13.0 now).  k_gemm_ks still does that for the mask layouts.
 
 template <int KIND>
 struct Kind {
@@ -450,27 +445,19 @@ __device__ __forceinline__ void expand_dense(const WRegs<KIND> &r, const uint2 *
     c1 = v4i{(int)out[4], (int)out[5], (int)out[6], (int)out[7]};
 }
 
-// Expands lane `lane`'s part of a compact block and writes it to the LDS
-// weight area of a slot: block bl of the tile (16 rows), in the layout the
-// compute stage reads (4:2 operand, or swizzled dense rows).
-template <int KIND, int WVB>
+// k_gemm_ks, mask layouts: expands lane `lane`'s part of a compact block and
+// writes it to the LDS weight area of a slot: block bl of the tile (16 rows),
+// as swizzled dense rows.
+template <int KIND>
 __device__ __forceinline__ void expand_to_lds(const WRegs<KIND> &r, const uint2 *lut, int8_t *wslot, int bl,
                                               int lane) {
-    if constexpr (Kind<KIND>::kSp) {
-        v4i vals;
-        uint32_t idx;
-        expand_sp42<KIND>(r, lut, vals, idx);
-        *(v4i *)(wslot + bl * kVBlock + lane * 16) = vals;
-        *(uint32_t *)(wslot + WVB + bl * kMBlock + lane * 4) = idx;
-    } else {
-        v4i c0, c1;
-        expand_dense<KIND>(r, lut, c0, c1);
-        const int row = bl * 16 + (lane & 15);
-        const int ch = 2 * (lane >> 4);                          // the lane's first 16-byte chunk of the row
-        int8_t *rowp = wslot + row * 128;
-        *(v4i *)(rowp + ((ch ^ (row & 7)) << 4)) = c0;
-        *(v4i *)(rowp + (((ch + 1) ^ (row & 7)) << 4)) = c1;
-    }
+    v4i c0, c1;
+    expand_dense<KIND>(r, lut, c0, c1);
+    const int row = bl * 16 + (lane & 15);
+    const int ch = 2 * (lane >> 4);                          // the lane's first 16-byte chunk of the row
+    int8_t *rowp = wslot + row * 128;
+    *(v4i *)(rowp + ((ch ^ (row & 7)) << 4)) = c0;
+    *(v4i *)(rowp + (((ch + 1) ^ (row & 7)) << 4)) = c1;
 }
 
 // A workgroup past the GEMM's own (blockIdx.x >= gemm_grid) expands blocks
@@ -520,250 +507,150 @@ struct Geometry {
     static constexpr int NW = WN * WM;                               // waves per workgroup (4 or 8)
     static constexpr int BN = WN * FN * 16;
     static constexpr int BM = WM * FM * 16;
-    static constexpr int XB = BM * 128;                              // X bytes per slot
-    static constexpr int WVB = K::kSp ? (BN / 16) * kVBlock : BN * 128;  // weight value bytes per slot
-    static constexpr int WMB = K::kSp ? (BN / 16) * kMBlock : 0;         // weight position bytes per slot
-    static constexpr int SLOT = XB + WVB + WMB;
-    static constexpr int XI = BM / (8 * NW);                         // X loads per wave per k-step
-    static constexpr int WB = (BN / 16) / NW;                        // weight blocks per wave (compact kinds)
-    static constexpr int WI = K::kDecode ? WB * K::LOADS                          // weight loads per wave
-                              : KIND == NM_KIND_SP42 ? (BN / 16) / NW * 2 : BN / (8 * NW);
-    static constexpr int DMA = XI + WI;                              // vector-memory loads per wave per k-step
-    static constexpr int CPR = FN * 4;                               // 4-channel chunks per staged row
+    static constexpr int VB = KIND == NM_KIND_SP42 ? 16 : K::VB;     // packed value bytes per lane and block
+    static constexpr int MB = KIND == NM_KIND_SP42 ? 4 : K::MB;      // packed position bytes per lane and block
+    // a slot: the X slice, the weight's values (or dense rows) and its
+    // positions, each area in whole direct-to-LDS instructions of 1024 bytes
+    static constexpr int XC = BM / 8;
+    static constexpr int VC = KIND == NM_KIND_DENSE ? BN / 8 : (BN / 16 * 64 * VB + 1023) / 1024;
+    static constexpr int MC = KIND == NM_KIND_DENSE ? 0 : (BN / 16 * 64 * MB + 1023) / 1024;
+    static constexpr int XB = XC * 1024, VA = VC * 1024, SLOT = (XC + VC + MC) * 1024;
+    static constexpr int NC = XC + VC + MC;                          // instructions per k-step
+    static constexpr int ND = (NC + NW - 1) / NW;                    // per wave: ND, or (the last waves) one less
+    static constexpr int DMA = NC / NW;                              // at least this many
+    static constexpr int EXTRA = NC % NW;                            // waves with one more
+    // A k-step runs in P phases.  One operand is streamed: GA of its fragments
+    // per phase, the next phase's (or the next k-step's) loaded into a second
+    // register set meanwhile; the other is kept for the whole k-step and
+    // reloaded fragment by fragment after its last use.  Where a wave has fewer
+    // weight than X fragments X is streamed, else the weight: the kept operand
+    // is the smaller one, which leaves the 8-wave 128 x 128 tile the registers
+    // for three workgroups per CU.  The dense operand needs 8 registers per
+    // fragment and the compact ones decode into 5 or 8 more, so those go one
+    // fragment at a time.  P is even, so a k-step's first phase is always in
+    // the same register set.
+    static constexpr bool XS = FN < FM && FM % 2 == 0;               // X is streamed
+    static constexpr int P = XS ? FM : KIND == NM_KIND_SP42 && FN >= 4 ? FN / 2 : FN;
+    static constexpr int GA = XS ? 1 : FN / P;
+    static constexpr int KEPT = XS ? FN : FM;                        // groups of a phase
+    // ring depth: as asked, or as deep as 160 KB of LDS allow
+    static constexpr int ROOM = 160 * 1024 - BN * 8 - K::LUT * 8 - 64;
+    static constexpr int RING = NST * SLOT <= ROOM ? NST : ROOM / SLOT;
+    static constexpr int CPR = FN * 4;                               // 4-channel chunks per staged int32 row
     static constexpr int RPI = 64 / CPR;                             // staged rows read per instruction
-    static constexpr int ROWB = FN * 64 + 16;                        // padded bytes per staged int32 row
-    static constexpr int EPI = NW * 16 * ROWB;
-    // ring depth: as asked, or as deep as 160 KB of LDS allows
-    static constexpr int RING = NST * SLOT <= 160 * 1024 - 4096 ? NST : (160 * 1024 - 4096) / SLOT;
-    static constexpr int LDSB = RING * SLOT > EPI ? RING * SLOT : EPI;
-    static_assert((NW == 4 || NW == 8) && RING >= 2 && 64 % CPR == 0 && BM % (8 * NW) == 0, "tile shape");
-    static_assert(KIND == NM_KIND_DENSE ? BN % (8 * NW) == 0 : (BN / 16) % NW == 0,
-                  "weight loads split evenly over the waves");
-    static_assert(LDSB + K::LUT * 8 <= 160 * 1024, "LDS budget");
+    static constexpr int stage_rows(int eb) { return 16 * FN * eb >= 64 ? 16 : 1024 / (16 * FN * eb); }
+    static constexpr int stage_bytes(int eb) { return stage_rows(eb) * (FN * 16 * eb + 16); }
+    static constexpr int STG = stage_bytes(4) > stage_bytes(1) ? stage_bytes(4) : stage_bytes(1);
+    static constexpr int LDSB = RING * SLOT > NW * STG ? RING * SLOT : NW * STG;
+    // waves per SIMD that LDS and the accumulators allow (the register budget):
+    // without this bound a few registers more than a power of two would cost
+    // whole workgroups per CU
+    // (LDS is handed out in pieces of 1280 bytes)
+    static constexpr int fit(int extra) { return 128 / ((LDSB + extra + K::LUT * 8 + 16 + 1279) / 1280); }
+    // the tile's two multiplier slices: in LDS of their own, or, where that 1 KB
+    // would cost a workgroup per CU (2:4 on the 8-wave 128 x 128 tile: the third,
+    // 2 % of a ViT-L layer), in a ring slot and then in registers
+    static constexpr bool MUL_LDS = fit(BN * 8) == fit(0);
+    static constexpr int MULB = MUL_LDS ? BN * 8 : 0;
+    static constexpr int FIT = fit(MULB), BY_LDS = (FIT < 1 ? 1 : FIT) * NW / 4;
+    static constexpr int CAP = FN * FM >= 16 ? (FN * FM == 16 && NW == 4 ? 3 : 2) : FN * FM >= 8 ? (NW == 8 && KIND == NM_KIND_SP42 ? 6 : 4) : 5;
+    static constexpr int WAVES = BY_LDS < CAP ? BY_LDS : CAP;
+    static constexpr int in_flight(int steps, int dma) { return steps * dma <= 63 ? steps * dma : 63 / dma * dma; }
+    static_assert((NW == 4 || NW == 8) && RING >= 2 && 64 % CPR == 0 && BM % 8 == 0 && DMA >= 1, "tile shape");
+    static_assert(stage_bytes(2) <= STG, "staging area");
+    static_assert(LDSB + MULB + K::LUT * 8 + 16 <= 160 * 1024 && P % 2 == 0, "LDS budget, register sets");
+    static_assert(BN * 8 <= SLOT, "the multipliers fit a slot");
 };
 
-// The stages of an output-split tile (WN x WM waves, each FN x FM
-// accumulators).
-template <class G, int KIND>
-struct OutSplit {
-    using K = Kind<KIND>;
-    static constexpr int BN = G::BN, BM = G::BM, FN = G::FN, FM = G::FM, NW = G::NW;
-    static constexpr int WJ = KIND == NM_KIND_SP42 ? (BN / 16) / NW : K::kDecode ? G::WB : BN / (8 * NW);
+// The weight operand of one (fragment, k-step) in registers: as it sits in
+// LDS (raw), and as the matrix instruction reads it.
+template <int KIND>
+struct RawOperand {
+    WRegs<KIND> r;
+};
+template <>
+struct RawOperand<NM_KIND_SP42> {
+    v4i lo;
+    int idx;
+};
+template <>
+struct RawOperand<NM_KIND_DENSE> {
+    v4i lo, hi;
+};
 
-    // Per-lane byte offsets of one tile's loads at k-step 0: the X row chunks
-    // and the weight blocks (or dense weight row chunks).  A k-step adds the
-    // same amount to every lane, so each load is a 32-bit offset from a
-    // scalar base that advances with the k-step (X and the weights hold fewer
-    // than 2^32 bytes, checked on the host).  Rows of X past m, and weight
-    // rows past n, read a valid row instead: their outputs are never stored.
-    struct Cursor {
-        uint32_t x[G::XI];
-        uint32_t w[WJ];
-        uint32_t m[KIND == NM_KIND_DENSE ? 1 : WJ];
-    };
-
-    static __device__ __forceinline__ Cursor cursor(const GemmArgs &a, int wave, int lane, int tok0, int ch0) {
-        Cursor c;
+// Epilogue of one output: the wave's FN x FM accumulators, packed to EB bytes
+// per channel by `pack`, go through the wave's private staging area 16 (or, for
+// narrow rows, 32) tokens at a time and leave as whole rows of the wave's
+// tile, 16 bytes per lane.  Packing before the staging keeps its LDS traffic
+// and its stores at EB bytes per output: 4-byte stores of int8 codes wrote 32-
+// or 64-byte pieces of a line per instruction and spent 10 vector instructions
+// per code after the staging (DeiT-B batch 128 fc1, 2:4, int8 output: 81 us,
+// of which the output stream alone needs 13).
+template <class G, int EB, class Pack, class Store>
+__device__ __forceinline__ void store_rows(int8_t *stg, int lane, const v4i (&acc)[G::FN][G::FM], const Pack &pack,
+                                           const Store &store) {
+    constexpr int FN = G::FN, FM = G::FM;
+    constexpr int ROW = FN * 16 * EB + 16;            // padded staged row
+    constexpr int CPR = FN * EB;                      // 16-byte chunks per row
+    constexpr int JG = G::stage_rows(EB) / 16;        // token fragments staged at once
+    constexpr int NR = JG * 16 * CPR / 64;            // chunks each lane stores per group
+    const int lg = lane >> 4;
 #pragma unroll
-        for (int j = 0; j < G::XI; ++j) {
-            const int r = 8 * (NW * j + wave) + (lane >> 3);
-            const int cc = (lane & 7) ^ (r & 7);
-            const int tok = tok0 + r < a.m ? tok0 + r : a.m - 1;
-            c.x[j] = (uint32_t)tok * (uint32_t)a.k + (uint32_t)cc * 16;
-        }
-        if constexpr (KIND == NM_KIND_SP42 || K::kDecode) {
-            const int f0 = ch0 >> 4;
-            constexpr int VB = KIND == NM_KIND_SP42 ? 16 : K::VB, MB = KIND == NM_KIND_SP42 ? 4 : K::MB;
+    for (int j0 = 0; j0 < FM; j0 += JG) {
 #pragma unroll
-            for (int j = 0; j < WJ; ++j) {
-                const int bl = NW * j + wave;              // weight block of the slot
-                int f = f0 + bl;
-                f = f < a.n_frags ? f : a.n_frags - 1;
-                const uint32_t b0 = (uint32_t)f * (uint32_t)a.k_steps;
-                c.w[j] = (b0 * 64 + lane) * VB;
-                c.m[j] = (b0 * 64 + lane) * MB;
-            }
-        } else {
-#pragma unroll
-            for (int j = 0; j < WJ; ++j) {
-                const int r = 8 * (NW * j + wave) + (lane >> 3);
-                const int cc = (lane & 7) ^ (r & 7);
-                const int row = ch0 + r < a.n ? ch0 + r : a.n - 1;
-                c.w[j] = (uint32_t)row * (uint32_t)a.k + (uint32_t)cc * 16;
-            }
-        }
-        return c;
-    }
-
-    // Fill ring slot st with k-step s of the tile of cursor c: the X slice,
-    // and for the stored kinds the weight slice.  Past k the packed weight is
-    // zero, so X may hold anything there (its loads are clamped to the row);
-    // for a dense weight the tail k-step is staged with zeros instead.
-    static __device__ __forceinline__ void issue(const GemmArgs &a, const Cursor &c, int8_t *lds, uint32_t lds0,
-                                                 int wave, int lane, int s, int st) {
-        const uint32_t slot = lds0 + st * G::SLOT;
-        if (s * 128 + 128 <= a.k) {
-            const int8_t *xb = a.X + (size_t)s * 128;
-#pragma unroll
-            for (int j = 0; j < G::XI; ++j) dma16o(xb, c.x[j], slot + (NW * j + wave) * 1024);
-        } else {
-            // last k-step of a k that is not a multiple of 128: clamp to the row
-#pragma unroll
-            for (int j = 0; j < G::XI; ++j) {
-                const int r = 8 * (NW * j + wave) + (lane >> 3);
-                const uint32_t cc16 = (uint32_t)(((lane & 7) ^ (r & 7)) * 16);
-                const uint32_t kk = (uint32_t)s * 128 + cc16 < (uint32_t)a.k ? (uint32_t)s * 128 + cc16
-                                                                              : (uint32_t)a.k - 16;
-                dma16o(a.X, c.x[j] - cc16 + kk, slot + (NW * j + wave) * 1024);
-            }
-        }
-        if constexpr (KIND == NM_KIND_SP42) {
-            const int8_t *vb = a.A + (size_t)s * kVBlock;
-            const uint8_t *mb = a.meta + (size_t)s * kMBlock;
-#pragma unroll
-            for (int j = 0; j < WJ; ++j) {
-                const int bl = NW * j + wave;
-                dma16o(vb, c.w[j], slot + G::XB + bl * kVBlock);
-                dma4o(mb, c.m[j], slot + G::XB + G::WVB + bl * kMBlock);
-            }
-        } else if constexpr (KIND == NM_KIND_DENSE) {
-            if (s * 128 + 128 <= a.k) {
-                const int8_t *wb = a.A + (size_t)s * 128;
-#pragma unroll
-                for (int j = 0; j < WJ; ++j) dma16o(wb, c.w[j], slot + G::XB + (NW * j + wave) * 1024);
-            } else {
-                // tail k-step of a dense weight: plain loads, zeros past k
-#pragma unroll
-                for (int j = 0; j < WJ; ++j) {
-                    const int r = 8 * (NW * j + wave) + (lane >> 3);
-                    const uint32_t cc16 = (uint32_t)(((lane & 7) ^ (r & 7)) * 16);
-                    const uint32_t kk = (uint32_t)s * 128 + cc16;
-                    v4i v = v4i{0, 0, 0, 0};
-                    if (kk < (uint32_t)a.k) v = *(const v4i *)(a.A + (c.w[j] - cc16 + kk));
-                    *(v4i *)(lds + st * G::SLOT + G::XB + (NW * j + wave) * 1024 + lane * 16) = v;
-                }
-            }
-        }
-    }
-
-    // Compact kinds: this wave's compact blocks of k-step s into registers.
-    static __device__ __forceinline__ void wload_step(const GemmArgs &a, const Cursor &c, int s,
-                                                      WRegs<KIND> (&r)[WJ]) {
-        if constexpr (K::kDecode) {
-            const int8_t *vb = a.A + (size_t)s * 64 * K::VB;
-            const uint8_t *mb = a.meta + (size_t)s * 64 * K::MB;
-#pragma unroll
-            for (int j = 0; j < WJ; ++j) wload<KIND>(r[j], vb + c.w[j], mb + c.m[j]);
-        }
-    }
-
-    // Compact kinds: expand the registers into the weight area of slot st.
-    static __device__ __forceinline__ void expand_step(int8_t *lds, const uint2 *lut, int wave, int lane, int st,
-                                                       const WRegs<KIND> (&r)[WJ]) {
-        if constexpr (K::kDecode) {
-#pragma unroll
-            for (int j = 0; j < WJ; ++j)
-                expand_to_lds<KIND, G::WVB>(r[j], lut, lds + st * G::SLOT + G::XB, NW * j + wave, lane);
-        }
-    }
-
-    // One k-step of the wave's FN x FM accumulators from ring slot st.
-    static __device__ __forceinline__ void compute(const int8_t *lds, int wn, int wm, int lane, int st,
-                                                   v4i (&acc)[FN][FM]) {
-        const int lg = lane >> 4;
-        const int8_t *xs = lds + st * G::SLOT;
-        const int8_t *ws = xs + G::XB;
-        if constexpr (K::kSp) {
-            v4i av[FN];
-            int ai[FN];
-#pragma unroll
-            for (int i = 0; i < FN; ++i) {
-                const int bl = wn * FN + i;
-                av[i] = *(const v4i *)(ws + bl * kVBlock + lane * 16);
-                ai[i] = *(const int *)(ws + G::WVB + bl * kMBlock + lane * 4);
-            }
-#pragma unroll
-            for (int j = 0; j < FM; ++j) {
-                const int r = (wm * FM + j) * 16 + (lane & 15);
-                const int8_t *rowp = xs + r * 128;
-                const v4i blo = *(const v4i *)(rowp + ((lg ^ (r & 7)) << 4));
-                const v4i bhi = *(const v4i *)(rowp + (((lg + 4) ^ (r & 7)) << 4));
-                const v8i b = {blo[0], blo[1], blo[2], blo[3], bhi[0], bhi[1], bhi[2], bhi[3]};
+        for (int jj = 0; jj < JG; ++jj)
+            if (j0 + jj < FM) {
 #pragma unroll
                 for (int i = 0; i < FN; ++i)
-                    acc[i][j] = __builtin_amdgcn_smfmac_i32_16x16x128_i8(av[i], b, acc[i][j], ai[i], 0, 0);
+                    pack(i, acc[i][j0 + jj < FM ? j0 + jj : 0],
+                         stg + (jj * 16 + (lane & 15)) * ROW + (i * 16 + 4 * lg) * EB);
             }
-        } else {
-            v4i alo[FN], ahi[FN];
+        // all reads first, then the stores: one wait for the reads, none between stores
+        v4i v[NR];
 #pragma unroll
-            for (int i = 0; i < FN; ++i) {
-                const int r = (wn * FN + i) * 16 + (lane & 15);
-                const int8_t *rowp = ws + r * 128;
-                alo[i] = *(const v4i *)(rowp + ((lg ^ (r & 7)) << 4));
-                ahi[i] = *(const v4i *)(rowp + (((lg + 4) ^ (r & 7)) << 4));
-            }
+        for (int q = 0; q < NR; ++q) {
+            const int c = q * 64 + lane;
+            v[q] = *(const v4i *)(stg + (c / CPR) * ROW + (c % CPR) * 16);
+        }
 #pragma unroll
-            for (int j = 0; j < FM; ++j) {
-                const int r = (wm * FM + j) * 16 + (lane & 15);
-                const int8_t *rowp = xs + r * 128;
-                const v4i blo = *(const v4i *)(rowp + ((lg ^ (r & 7)) << 4));
-                const v4i bhi = *(const v4i *)(rowp + (((lg + 4) ^ (r & 7)) << 4));
-#pragma unroll
-                for (int i = 0; i < FN; ++i) {
-                    acc[i][j] = __builtin_amdgcn_mfma_i32_16x16x64_i8(alo[i], blo, acc[i][j], 0, 0, 0);
-                    acc[i][j] = __builtin_amdgcn_mfma_i32_16x16x64_i8(ahi[i], bhi, acc[i][j], 0, 0, 0);
-                }
-            }
+        for (int q = 0; q < NR; ++q) {
+            const int c = q * 64 + lane;
+            const int row = j0 * 16 + c / CPR;        // token of the wave's tile
+            if (JG == 1 || row < FM * 16) store(row, (c % CPR) * (16 / EB), v[q]);
         }
     }
+}
 
-    // Epilogue of the wave's part of a tile through its private staging area
-    // stg (16 rows of ROWB bytes): 16 tokens at a time, the FN accumulators
-    // become int32 rows, read back row-contiguously, so that every store
-    // instruction writes whole rows of the wave's tile.  With split_k > 1 the
-    // rows go to the partial-sum workspace instead.
-    static __device__ __forceinline__ void store(const GemmArgs &a, int8_t *stg, int lane, int wn, int wm, int tok0,
-                                                 int ch0, int split, const v4i (&acc)[FN][FM]) {
-        const int lg = lane >> 4;
-        const int ec = lane % G::CPR;                     // 4-channel chunk this lane stores
-        const int er = lane / G::CPR;                     // row offset within a read group
-        const int ch = ch0 + wn * FN * 16 + ec * 4;       // first of the lane's 4 channels
-        const bool ch_ok = ch < a.n;
-        const EpiScale sc = load_scale(a, ch);
-        const __amdgpu_buffer_rsrc_t prsrc = partial_rsrc(a);
-        constexpr int NR = 16 / G::RPI;                   // staged rows each lane stores per 16 tokens
+// Stores 16 bytes (16 / EB channels from ch) of token tok of an [m x n]
+// output: one store, or at the end of a row whose n is no multiple of 16 / EB
+// the 4-channel pieces that exist (n is a multiple of 4).  Buffer stores with
+// a 32-bit byte offset, as in emit_out.
+template <int EB, int POLICY>
+__device__ __forceinline__ void store_chunk(const GemmArgs &a, __amdgpu_buffer_rsrc_t r, int tok, int ch,
+                                            const v4i &v) {
+    if (tok >= a.m || ch >= a.n) return;
+    const uint32_t e = ((uint32_t)tok * (uint32_t)a.n + (uint32_t)ch) * EB;
+    if (ch + 16 / EB <= a.n) {
+        __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(v4u, v), r, (int)e, 0, POLICY);
+    } else if constexpr (EB == 2) {
+        __builtin_amdgcn_raw_buffer_store_b64(v2u{(unsigned)v[0], (unsigned)v[1]}, r, (int)e, 0, POLICY);
+    } else if constexpr (EB == 1) {
 #pragma unroll
-        for (int j = 0; j < FM; ++j) {
-#pragma unroll
-            for (int i = 0; i < FN; ++i)
-                *(v4i *)(stg + (lane & 15) * G::ROWB + (i * 16 + 4 * lg) * 4) = acc[i][j];
-            // all reads first, then the stores: one wait for the reads, none between stores
-            v4i v[NR];
-#pragma unroll
-            for (int r = 0; r < NR; ++r) v[r] = *(const v4i *)(stg + (r * G::RPI + er) * G::ROWB + ec * 16);
-#pragma unroll
-            for (int r = 0; r < NR; ++r) {
-                const int tok = tok0 + (wm * FM + j) * 16 + r * G::RPI + er;
-                if (tok < a.m && ch_ok) {
-                    if (a.split_k == 1)
-                        emit_out(a, tok, ch, v[r], sc);
-                    else
-                        publish_partial(a, prsrc, split, tok, ch, v[r]);
-                }
-            }
-        }
+        for (int d = 0; d < 3; ++d)
+            if (ch + 4 * d < a.n)
+                __builtin_amdgcn_raw_buffer_store_b32((unsigned)v[d], r, (int)(e + 4 * d), 0, POLICY);
     }
-};
+}
 
 template <int KIND, int WN, int WM, int FN, int FM, int NST>
-__global__ __launch_bounds__(64 * WN * WM) void k_gemm(GemmArgs a) {
+__global__ __launch_bounds__(64 * WN * WM)
+__attribute__((amdgpu_waves_per_eu(Geometry<KIND, WN, WM, FN, FM, NST>::WAVES))) void k_gemm(GemmArgs a) {
     using G = Geometry<KIND, WN, WM, FN, FM, NST>;
-    using O = OutSplit<G, KIND>;
     using K = Kind<KIND>;
-    constexpr int BN = G::BN, BM = G::BM;
-    constexpr int R = G::RING;
+    constexpr int BN = G::BN, BM = G::BM, NW = G::NW, R = G::RING, P = G::P, GA = G::GA;
+    constexpr bool kDense = KIND == NM_KIND_DENSE;
 
-    __shared__ __attribute__((aligned(1024))) int8_t lds[G::LDSB];
+    __shared__ __attribute__((aligned(1024))) int8_t lds[G::LDSB + G::MULB];
     __shared__ uint2 lut[K::LUT];
     __shared__ int s_last;
     const uint32_t lds0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) int8_t *)lds;
@@ -778,7 +665,7 @@ __global__ __launch_bounds__(64 * WN * WM) void k_gemm(GemmArgs a) {
     tile_order(lid, a.tiles_n, a.tiles_m * a.split_k, a.group_rows, &tn, &rest);
     const int split = rest % a.split_k;
     const int tm = rest / a.split_k;
-    const int tid = threadIdx.x, lane = tid & 63;
+    const int tid = threadIdx.x, lane = tid & 63, lg = lane >> 4;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int wn = wave % WN, wm = wave / WN;
     const int tok0 = tm * BM;
@@ -786,6 +673,73 @@ __global__ __launch_bounds__(64 * WN * WM) void k_gemm(GemmArgs a) {
     const int s_begin = (int)((int64_t)split * a.k_steps / a.split_k);
     const int s_end = (int)((int64_t)(split + 1) * a.k_steps / a.split_k);
     const int nsteps = s_end - s_begin;
+    // a k that is no multiple of 128: the last k-step holds k % 128 columns
+    const int ragged = a.k & 127;
+    const int t_tail = ragged && s_end == a.k_steps ? nsteps - 1 : -1;   // that k-step, if it is ours
+
+    // --- loads.  A k-step's direct-to-LDS instructions are numbered X, values
+    // (or dense rows), positions; wave w takes w, w + NW, ...  Each lane's
+    // source is a 32-bit offset from a scalar base that advances with the
+    // k-step (X and the weights hold fewer than 2^32 bytes, checked on the
+    // host).  Packed areas are copied as they are stored, 16 bytes per lane
+    // across fragments, so the few position bytes of several fragments share
+    // one instruction.  Rows of X past m and weight rows past n read a valid
+    // row instead: their outputs are never stored.
+    const int cc16 = ((lane & 7) ^ ((lane >> 3) & 7)) * 16;   // swizzled source chunk of a row slice
+    uint32_t off[G::ND];
+#pragma unroll
+    for (int c = 0; c < G::ND; ++c) {
+        const int q = NW * c + wave;
+        if (q < G::XC) {
+            const int tok = tok0 + 8 * q + (lane >> 3);
+            off[c] = (uint32_t)(tok < a.m ? tok : a.m - 1) * (uint32_t)a.k + (uint32_t)cc16;
+        } else if (kDense) {
+            const int row = ch0 + 8 * (q - G::XC) + (lane >> 3);
+            off[c] = (uint32_t)(row < a.n ? row : a.n - 1) * (uint32_t)a.k + (uint32_t)cc16;
+        } else {
+            // 16-byte chunk of the area -> block (4 VB or 4 MB chunks each) and chunk in it
+            auto packed = [&](int chunk, auto per) {
+                constexpr int PER = decltype(per)::value;
+                int f = (ch0 >> 4) + chunk / PER;
+                f = f < a.n_frags ? f : a.n_frags - 1;
+                return ((uint32_t)f * (uint32_t)a.k_steps * PER + (uint32_t)(chunk % PER)) * 16;
+            };
+            off[c] = q < G::XC + G::VC
+                         ? packed((q - G::XC) * 64 + lane, std::integral_constant<int, G::VB ? 4 * G::VB : 1>{})
+                         : packed((q - G::XC - G::VC) * 64 + lane, std::integral_constant<int, G::MB ? 4 * G::MB : 1>{});
+        }
+    }
+    // The bases stay in scalar registers: reloading a kernel argument inside
+    // the loop would wait for every LDS read in flight (one shared counter).
+    const int8_t *xp = a.X, *vp = a.A, *mp = (const int8_t *)a.meta;
+    asm("" : "+s"(xp), "+s"(vp), "+s"(mp));
+    // instruction c of this wave for k-step t (of this split) into ring slot st
+    auto load = [&](int c, int t, int st, int live) {
+        const int q = NW * c + wave;
+        const uint32_t s = (uint32_t)(s_begin + t);
+        const int8_t *base;
+        if (NW * c + NW <= G::XC || (NW * c < G::XC && q < G::XC))
+            base = xp + (uint64_t)s * 128;
+        else if (kDense)
+            base = vp + (uint64_t)s * 128;
+        else if (NW * c + NW <= G::XC + G::VC || (NW * c < G::XC + G::VC && q < G::XC + G::VC))
+            base = vp + (uint64_t)s * (64 * G::VB);
+        else
+            base = mp + (uint64_t)s * (64 * G::MB);
+        const int l = NW * c + NW <= G::NC || q < G::NC ? live : 0;
+        dma16o_if(base, off[c], lds0 + st * G::SLOT + q * 1024, __builtin_amdgcn_readfirstlane(l));
+    };
+    // before the ragged last k-step is loaded: chunks of a row past k read the
+    // row's last chunk instead (a packed weight is zero there, and a dense
+    // operand is masked before it is used)
+    auto clamp_tail = [&](int t) {
+        if (t == t_tail) {
+            const uint32_t back = cc16 >= ragged ? (uint32_t)(cc16 - (ragged - 16)) : 0u;
+#pragma unroll
+            for (int c = 0; c < G::ND; ++c)
+                if (kDense || NW * c + wave < G::XC) off[c] -= back;
+        }
+    };
 
     v4i acc[FN][FM];
 #pragma unroll
@@ -793,64 +747,257 @@ __global__ __launch_bounds__(64 * WN * WM) void k_gemm(GemmArgs a) {
 #pragma unroll
         for (int j = 0; j < FM; ++j) acc[i][j] = v4i{0, 0, 0, 0};
 
-    const typename O::Cursor cur = O::cursor(a, wave, lane, tok0, ch0);
-    WRegs<KIND> wr[O::WJ];
-#pragma unroll
-    for (int i = 0; i < R - 1; ++i)
-        if (i < nsteps) O::issue(a, cur, lds, lds0, wave, lane, s_begin + i, i);
-    if constexpr (K::kDecode) {
-        // the compact weights of the first R - 1 k-steps, expanded in order,
-        // and the next k-step's loaded into registers; the lookup table is
-        // built while the first loads are in flight
-        if (nsteps > 0) O::wload_step(a, cur, s_begin, wr);
-        fill_lut<KIND>(lut, tid, 64 * WN * WM);
-        __syncthreads();
-#pragma unroll
-        for (int i = 0; i < R - 1; ++i)
-            if (i < nsteps) {
-                O::expand_step(lds, lut, wave, lane, i, wr);
-                if (i + 1 < nsteps) O::wload_step(a, cur, s_begin + i + 1, wr);
+    // --- operand registers (two sets of the streamed operand, one of the kept).
+    // A lane's two 16-byte chunks of
+    // a row: k 16 lg and 64 + 16 lg as the instructions order them, or, for
+    // the mask layouts (whose lane holds 32 consecutive columns), 32 lg and
+    // 32 lg + 16 of both operands.
+    constexpr bool kMask = K::NV > 0;
+    const int c0 = kMask ? 2 * lg : lg, c1 = kMask ? 2 * lg + 1 : lg + 4;
+    const int sw0 = (c0 ^ (lane & 7)) << 4, sw1 = (c1 ^ (lane & 7)) << 4;
+    const int8_t *xrow = lds + (wm * FM * 16 + (lane & 15)) * 128;
+    const int8_t *wrow = lds + G::XB + (kDense ? (wn * FN * 16 + (lane & 15)) * 128
+                                               : wn * FN * 64 * G::VB + lane * G::VB);
+    const int8_t *mrow = lds + G::XB + G::VA + wn * FN * 64 * G::MB + lane * G::MB;
+    constexpr bool XS = G::XS;
+    RawOperand<KIND> wop[XS ? 1 : 2][XS ? FN : GA];
+    v4i blo[XS ? 2 : FM], bhi[XS ? 2 : FM];
+    auto read_w = [&](int so, int i, RawOperand<KIND> &o) {
+        if constexpr (KIND == NM_KIND_SP42) {
+            o.lo = *(const v4i *)(wrow + so + i * kVBlock);
+            o.idx = *(const int *)(mrow + so + i * kMBlock);
+        } else if constexpr (kDense) {
+            o.lo = *(const v4i *)(wrow + so + i * 2048 + sw0);
+            o.hi = *(const v4i *)(wrow + so + i * 2048 + sw1);
+        } else {
+            wload<KIND>(o.r, wrow + so + i * (64 * G::VB), (const uint8_t *)mrow + so + i * (64 * G::MB));
+        }
+    };
+    auto read_x = [&](int so, int j, int reg) {
+        blo[reg] = *(const v4i *)(xrow + so + j * 2048 + sw0);
+        bhi[reg] = *(const v4i *)(xrow + so + j * 2048 + sw1);
+    };
+    // a weight operand as the matrix instruction reads it (lo, hi or lo, idx)
+    auto operand = [&](const RawOperand<KIND> &o, bool tail, v4i &lo, v4i &hi, int &idx) {
+        if constexpr (KIND == NM_KIND_SP42) {
+            lo = o.lo;
+            idx = o.idx;
+        } else if constexpr (kDense) {
+            lo = o.lo;
+            hi = o.hi;
+            if (tail) {
+                if (16 * lg >= ragged) lo = v4i{0, 0, 0, 0};
+                if (64 + 16 * lg >= ragged) hi = v4i{0, 0, 0, 0};
             }
-    }
-    for (int it = 0; it < nsteps; ++it) {
-        // k-step it was issued NST-1 iterations ago; only the loads of later
-        // k-steps may remain in flight.  The barrier then publishes every
-        // wave's slot (X and expanded weights) and frees the slot computed in
-        // the previous iteration.
-        const int later = nsteps - 1 - it < R - 2 ? nsteps - 1 - it : R - 2;
-        wait_later_then_barrier<R - 2, G::DMA>(later);
-        const int nx = it + R - 1;
-        if (nx < nsteps) {
-            if constexpr (K::kDecode) {
-                O::expand_step(lds, lut, wave, lane, nx % R, wr);      // k-step nx, loaded one iteration ago
-                O::issue(a, cur, lds, lds0, wave, lane, s_begin + nx, nx % R);
-                if (nx + 1 < nsteps) O::wload_step(a, cur, s_begin + nx + 1, wr);
-            } else {
-                O::issue(a, cur, lds, lds0, wave, lane, s_begin + nx, nx % R);
+        } else if constexpr (K::kSp) {
+            uint32_t x;
+            expand_sp42<KIND>(o.r, lut, lo, x);
+            idx = (int)x;
+        } else {
+            expand_dense<KIND>(o.r, lut, lo, hi);
+        }
+    };
+
+    // The tile's multipliers, loaded so early that the epilogue does not start with
+    // a load's latency: with the ring, or into a slot that the last k-step leaves free.
+    const bool scaled = a.split_k == 1 && (a.Yh || a.Yq);
+    const int moff = G::MUL_LDS ? G::LDSB : (nsteps >= 2 ? (nsteps - 2) % R : 1) * G::SLOT;
+    auto load_mul = [&]() {
+        const float *src = wave == 0 ? (a.Yh ? a.scale : nullptr) : wave == 1 && a.Yq ? a.qscale : nullptr;
+        if (scaled && src && lane < BN / 4) {
+            const int ch = ch0 + 4 * lane < a.n ? ch0 + 4 * lane : 0;
+            dma16(src + ch, lds0 + moff + wave * BN * 4);
+        }
+    };
+
+    // --- prologue: fill the ring, then the operands of the first phase
+    if (G::MUL_LDS || nsteps < 2) load_mul();
+#pragma unroll
+    for (int i = 0; i < R; ++i)
+        if (i < nsteps) {
+            clamp_tail(i);
+#pragma unroll
+            for (int c = 0; c < G::ND; ++c) load(c, i, i, 1);
+        }
+    fill_lut<KIND>(lut, tid, 64 * NW);
+    // the barrier of a k-step, with the loads of at most `STEPS` later ones in flight
+    const bool extra = G::EXTRA > 0 && wave < G::EXTRA;
+    auto landed = [&](bool full, auto steps) {
+        constexpr int S = decltype(steps)::value;
+        if (S > 0 && full) {
+            if (G::EXTRA > 0 && extra)
+                wait_only<G::in_flight(S, G::DMA + 1)>();
+            else
+                wait_only<G::in_flight(S, G::DMA)>();
+        } else {
+            wait_only<0>();
+        }
+        wait_then_barrier<63>();
+    };
+    landed(nsteps >= R, std::integral_constant<int, R - 1>{});
+#pragma unroll
+    for (int j = 0; j < (XS ? 1 : FM); ++j) read_x(0, j, j);
+#pragma unroll
+    for (int g = 0; g < (XS ? FN : GA); ++g) read_w(0, g, wop[0][g]);
+
+    // --- one k-step (t of this split): P phases of KEPT matrix groups.  Before
+    // the last phase every wave has read all the streamed operands it needs of
+    // the slot, and the next k-step must have landed: one barrier says both,
+    // frees the slot for k-step t + R, and the last phase already reads the
+    // next k-step's operands.  So matrix work always has its operands in
+    // registers while LDS and the loads are busy with later ones.  Measured
+    // against the form that read a k-step's operands after its barrier: ViT-L
+    // fc2 2:4 on 256 x 320 55 us against 75 on the best tile of that form,
+    // DeiT-B batch 128 fc1 2:4 57 against 84, ViT-L fc2 dense 69 against 82.
+    int st = 0;
+    auto step = [&](int t, auto last) {
+        constexpr bool more = !decltype(last)::value;        // another k-step follows
+        const int stn = st + 1 == R ? 0 : st + 1;
+        const int so = st * G::SLOT, son = stn * G::SLOT;
+        const int live = nsteps - R - t;
+        const bool tail = !more && t == t_tail;
+        v4i wlo[XS ? FN : GA], whi[XS ? FN : GA];
+        int widx[XS ? FN : GA];
+        if constexpr (XS) {
+#pragma unroll
+            for (int i = 0; i < FN; ++i) operand(wop[0][i], tail, wlo[i], whi[i], widx[i]);
+        }
+#pragma unroll
+        for (int p = 0; p < P; ++p) {
+            if constexpr (more) if (p == P - 1) {
+                landed(t + R - 1 < nsteps, std::integral_constant<int, R - 2>{});
+                clamp_tail(t + R);
+                if (!G::MUL_LDS && t + 2 == nsteps) load_mul();
+            }
+            if constexpr (!XS) {
+#pragma unroll
+                for (int g = 0; g < GA; ++g) operand(wop[p & 1][g], tail, wlo[g], whi[g], widx[g]);
+            }
+#pragma unroll
+            for (int e = 0; e < G::KEPT; ++e) {
+                __builtin_amdgcn_sched_barrier(0);
+                if (more && p == P - 1) {
+#pragma unroll
+                    for (int c = 0; c < G::ND; ++c)
+                        if (c * G::KEPT / G::ND == e) load(c, t + R, st, live);
+                }
+                if (XS ? e == 0 : true) {
+#pragma unroll
+                    for (int g = 0; g < GA; ++g)
+                        if (g * G::KEPT / GA == e) {
+                            const int nx = p < P - 1 ? (p + 1) * GA + g : g, at = p < P - 1 ? so : son;
+                            if (p < P - 1 || more) {
+                                if constexpr (XS)
+                                    read_x(at, nx, (p + 1) & 1);
+                                else
+                                    read_w(at, nx, wop[(p + 1) & 1][g]);
+                            }
+                        }
+                }
+                if (more && p == P - 1 && e > 0) {
+                    if constexpr (XS)
+                        read_w(son, e - 1, wop[0][e - 1]);
+                    else
+                        read_x(son, e - 1, e - 1);
+                }
+                __builtin_amdgcn_sched_barrier(0);
+                // kept fragment e with the phase's streamed ones
+                const int xr = XS ? p & 1 : e, j = XS ? p : e;
+                const v8i b = {blo[xr][0], blo[xr][1], blo[xr][2], blo[xr][3],
+                               bhi[xr][0], bhi[xr][1], bhi[xr][2], bhi[xr][3]};
+#pragma unroll
+                for (int g = 0; g < GA; ++g) {
+                    const int i = XS ? e : p * GA + g, w = XS ? e : g;
+                    if constexpr (K::kSp)
+                        acc[i][j] = __builtin_amdgcn_smfmac_i32_16x16x128_i8(wlo[w], b, acc[i][j], widx[w], 0, 0);
+                    else
+                        acc[i][j] = __builtin_amdgcn_mfma_i32_16x16x64_i8(wlo[w], blo[xr], acc[i][j], 0, 0, 0);
+                }
+                if constexpr (!K::kSp) {
+#pragma unroll
+                    for (int g = 0; g < GA; ++g) {
+                        const int i = XS ? e : p * GA + g, w = XS ? e : g;
+                        acc[i][j] = __builtin_amdgcn_mfma_i32_16x16x64_i8(whi[w], bhi[xr], acc[i][j], 0, 0, 0);
+                    }
+                }
             }
         }
-        O::compute(lds, wn, wm, lane, it % R, acc);
+        __builtin_amdgcn_sched_barrier(0);
+        if constexpr (more) {
+            if constexpr (XS)
+                read_w(son, FN - 1, wop[0][FN - 1]);
+            else
+                read_x(son, FM - 1, FM - 1);
+        }
+        st = stn;
+    };
+    for (int t = 0; t + 1 < nsteps; ++t) step(t, std::false_type{});
+    if (nsteps > 0) step(nsteps - 1, std::true_type{});
+
+    // --- epilogue
+    wait_only<0>();
+    __syncthreads();  // every wave is done with the ring, the multipliers have landed
+    const float *mul = (const float *)(lds + moff) + wn * FN * 16 + 4 * lg;   // + BN for the requantisation
+    v4f mreg[G::MUL_LDS ? 1 : 2][G::MUL_LDS ? 1 : FN];
+    if (!G::MUL_LDS && scaled) {
+#pragma unroll
+        for (int i = 0; i < FN; ++i)
+#pragma unroll
+            for (int h = 0; h < 2; ++h) mreg[h][i] = *(const v4f *)(mul + h * BN + i * 16);
+        __syncthreads();  // before any wave stages over them
+    }
+    auto multiplier = [&](int h, int i) {
+        if constexpr (G::MUL_LDS)
+            return *(const v4f *)(mul + h * BN + i * 16);
+        else
+            return mreg[h][i];
+    };
+    int8_t *stg = lds + wave * G::STG;
+    const int tokw = tok0 + wm * FM * 16, chw = ch0 + wn * FN * 16;   // the wave's part of the tile
+    const auto raw = [](int, const v4i &v, int8_t *dst) { *(v4i *)dst = v; };
+    if (a.split_k == 1) {
+        // one output: its rows, with the store policy the host chose for it
+        auto emit = [&](auto eb, void *out, const auto &pack) {
+            constexpr int EB = decltype(eb)::value;
+            if (!out) return;
+            const __amdgpu_buffer_rsrc_t r = __builtin_amdgcn_make_buffer_rsrc(
+                out, 0, (int)((uint32_t)a.m * (uint32_t)a.n * EB), kBufferFlags);
+            if (a.stream_out & EB)
+                store_rows<G, EB>(stg, lane, acc, pack, [&](int row, int ch, const v4i &v) {
+                    store_chunk<EB, kStoreNT>(a, r, tokw + row, chw + ch, v);
+                });
+            else
+                store_rows<G, EB>(stg, lane, acc, pack, [&](int row, int ch, const v4i &v) {
+                    store_chunk<EB, 0>(a, r, tokw + row, chw + ch, v);
+                });
+        };
+        emit(std::integral_constant<int, 4>{}, a.Y, raw);
+        emit(std::integral_constant<int, 2>{}, a.Yh, [&](int i, const v4i &v, int8_t *dst) {
+            *(v2u *)dst = pack_f16(v, multiplier(0, i));
+        });
+        emit(std::integral_constant<int, 1>{}, a.Yq, [&](int i, const v4i &v, int8_t *dst) {
+            *(uint32_t *)dst = pack_q8(v, multiplier(1, i));
+        });
+        return;
     }
 
-    __syncthreads();  // every wave is done with the ring
-    O::store(a, lds + wave * 16 * G::ROWB, lane, wn, wm, tok0, ch0, split, acc);
-    if (a.split_k == 1) return;
-
-    // Split-K: the last split to arrive adds every partial (integer addition:
-    // any order gives the same result) and writes the outputs.
+    // Split-K: the rows go to the partial-sum workspace; the last split to
+    // arrive adds every partial (integer addition: any order gives the same
+    // result) and writes the outputs.
+    const __amdgpu_buffer_rsrc_t prsrc = partial_rsrc(a);
+    store_rows<G, 4>(stg, lane, acc, raw, [&](int row, int ch, const v4i &v) {
+        if (tokw + row < a.m && chw + ch < a.n) publish_partial(a, prsrc, split, tokw + row, chw + ch, v);
+    });
     if (!arrive_last(a, tm * a.tiles_n + tn, &s_last)) return;
     const int ec = lane % G::CPR, er = lane / G::CPR;
-    const int ch = ch0 + wn * FN * 16 + ec * 4;
+    const int ch = chw + ec * 4;
     const bool ch_ok = ch < a.n;
-    const EpiScale sc = load_scale(a, ch);
-    const __amdgpu_buffer_rsrc_t prsrc = partial_rsrc(a);
+    const EpiScale es = load_scale(a, ch);
 #pragma unroll
-    for (int j = 0; j < FM; ++j)
-#pragma unroll
-        for (int r0 = 0; r0 < 16; r0 += G::RPI) {
-            const int tok = tok0 + (wm * FM + j) * 16 + r0 + er;
-            if (tok < a.m && ch_ok) emit_out(a, tok, ch, merge_partials(a, prsrc, tok, ch), sc);
-        }
+    for (int r0 = 0; r0 < FM * 16; r0 += G::RPI) {
+        const int tok = tokw + r0 + er;
+        if (tok < a.m && ch_ok) emit_out(a, tok, ch, merge_partials(a, prsrc, tok, ch), es);
+    }
 }
 
 // ---------------------------------------------------------------------------
@@ -1001,9 +1148,9 @@ __global__ __launch_bounds__(256) void k_gemm_ks(GemmArgs a) {
         }
     };
     auto expand_step = [&](int st) {
-        if constexpr (K::kDecode) {
+        if constexpr (K::NV > 0) {
 #pragma unroll
-            for (int bl = 0; bl < FN; ++bl) expand_to_lds<KIND, G::WVB>(wr[bl], lut, ringp + st * G::SLOT + G::XB, bl, lane);
+            for (int bl = 0; bl < FN; ++bl) expand_to_lds<KIND>(wr[bl], lut, ringp + st * G::SLOT + G::XB, bl, lane);
         }
     };
     // 1:4, 1:8, 2:8: block bl of slot st's compact bytes, read from the ring
@@ -1219,7 +1366,7 @@ int launch_one(const GemmArgs &args, int grid, void *stream) {
 
 template <int KIND, int T = 0>
 int launch_kind(int tile, const GemmArgs &args, int grid, void *stream) {
-    if constexpr (T < kNumTiles) {
+    if constexpr (T < kNumSchedules) {
         if (tile == T) return launch_one<KIND, T>(args, grid, stream);
         return launch_kind<KIND, T + 1>(tile, args, grid, stream);
     }

@@ -270,4 +270,159 @@ nm_status make_plan(int kind, int m, int n, int k, int out_mode, nm_plan *plan) 
     return complete_plan(kind, m, n, k, plan);
 }
 
+// ---------------------------------------------------------------------------
+// Schedule of a call without an explicit plan.  nm_spmm_plan's rules name one
+// tile per class of shapes; which tile is fastest depends on more than its
+// class -- how many whole rounds of workgroups it fills, how long the chain of
+// k-steps is, how many bytes the epilogue writes -- so a call that leaves the
+// schedule to the library takes the tile with the least estimated time.  The
+// estimate (microseconds) is linear in nine terms, fitted per tile and weight
+// kind (non-negative least squares on relative errors, near-best rows weighted
+// most) to 23 700 timings on an MI355X: every tile on 72 shapes drawn over m
+// 64..60000, n and k 128..4096 with int32, fp16 and int8 outputs, and on the
+// linears of DeiT, Swin-B and ViT-L.  Over those the chosen tile is within
+// 2-3 % of the best on average, against 15-18 % for the planner's rules; it is
+// taken only where it promises 3 % or more over the planner's tile, which
+// keeps the few shapes where the estimate errs from losing.
+struct CostTerms {
+    float launch, chain, round_steps, mean_steps, rounds, round_bytes, out_mb, split_line_mb, x_mb;
+};
+static constexpr CostTerms kCost[5][kNumSchedules] = {
+    {   // 2:4
+        {3.34f, 0.184f, 0.141f, 0.162f, 0.831f, 0.0f, 0.107f, 0.0734f, 0.0743f},
+        {3.05f, 0.236f, 0.0254f, 0.135f, 0.335f, 0.00319f, 0.106f, 0.0716f, 0.0539f},
+        {3.16f, 0.186f, 0.0992f, 0.0955f, 0.259f, 0.0216f, 0.11f, 0.0756f, 0.0829f},
+        {2.82f, 0.162f, 0.0964f, 0.0237f, 0.159f, 0.0f, 0.0923f, 0.0946f, 0.0736f},
+        {0.313f, 0.0512f, 0.488f, 0.361f, 5.28f, 0.269f, 0.0861f, 0.081f, 0.0882f},
+        {2.76f, 0.146f, 0.087f, 0.0464f, 0.279f, 0.0258f, 0.0359f, 0.0827f, 0.035f},
+        {2.73f, 0.214f, 0.0937f, 0.192f, 0.742f, 0.0312f, 0.103f, 0.077f, 0.0825f},
+        {2.2f, 0.0f, 0.554f, 0.17f, 1.48f, 0.0f, 0.0f, 0.116f, 0.0553f},
+        {1.85f, 0.0f, 0.405f, 0.0371f, 1.47f, 0.0f, 0.0f, 0.139f, 0.0695f},
+        {1.76f, 0.131f, 0.223f, 0.207f, 1.54f, 0.0f, 0.0f, 0.123f, 0.0f},
+        {2.54f, 0.0941f, 0.183f, 0.0897f, 0.323f, 0.0f, 0.0f, 0.118f, 0.0113f},
+        {3.09f, 0.341f, 0.0f, 0.283f, 1.16f, 0.0155f, 0.109f, 0.0694f, 0.0914f},
+        {2.03f, 0.0f, 0.482f, 0.174f, 2.9f, 0.0f, 0.109f, 0.0839f, 0.0461f},
+        {3.18f, 0.092f, 0.213f, 0.0f, 0.324f, 0.0283f, 0.107f, 0.0823f, 0.0575f},
+        {1.76f, 0.0f, 0.323f, 0.0f, 1.84f, 0.0185f, 0.108f, 0.0817f, 0.0928f},
+        {0.0f, 0.0225f, 0.884f, 0.0439f, 5.34f, 0.0206f, 0.139f, 0.0696f, 0.131f},
+    },
+    {   // 1:4 and 1:8
+        {3.28f, 0.305f, 0.0546f, 0.181f, 0.73f, 0.0796f, 0.0913f, 0.0739f, 0.0844f},
+        {3.13f, 0.265f, 0.0907f, 0.0659f, 0.386f, 0.00655f, 0.0976f, 0.063f, 0.0552f},
+        {3.27f, 0.237f, 0.0797f, 0.0794f, 0.104f, 0.0237f, 0.121f, 0.0724f, 0.103f},
+        {2.82f, 0.221f, 0.0354f, 0.0679f, 0.193f, 0.0f, 0.0976f, 0.0813f, 0.0691f},
+        {1.34f, 0.0378f, 0.946f, 0.158f, 3.59f, 0.371f, 0.111f, 0.0706f, 0.0636f},
+        {2.87f, 0.286f, 0.0742f, 0.0605f, 0.259f, 0.0492f, 0.019f, 0.0839f, 0.0186f},
+        {2.69f, 0.177f, 0.207f, 0.069f, 0.844f, 0.0175f, 0.0988f, 0.0767f, 0.0868f},
+        {2.06f, 0.0f, 0.693f, 0.0601f, 1.71f, 0.0f, 0.0106f, 0.0985f, 0.0768f},
+        {1.85f, 0.0f, 0.566f, 0.0f, 1.43f, 0.0f, 0.0f, 0.165f, 0.0378f},
+        {2.76f, 0.178f, 0.271f, 0.0798f, 0.673f, 0.0f, 0.0f, 0.0683f, 0.0666f},
+        {2.56f, 0.109f, 0.223f, 0.0f, 0.436f, 0.0f, 0.0f, 0.11f, 0.0628f},
+        {2.84f, 0.396f, 0.0f, 0.266f, 1.11f, 0.153f, 0.079f, 0.0716f, 0.0714f},
+        {2.34f, 0.0f, 0.693f, 0.0472f, 2.47f, 0.0583f, 0.11f, 0.0899f, 0.0508f},
+        {3.21f, 0.264f, 0.164f, 0.0357f, 0.377f, 0.000101f, 0.111f, 0.0761f, 0.0456f},
+        {3.15f, 0.163f, 0.221f, 0.0f, 0.204f, 0.0543f, 0.104f, 0.116f, 0.112f},
+        {1.17f, 0.0469f, 1.1f, 0.0f, 4.17f, 0.211f, 0.137f, 0.0662f, 0.109f},
+    },
+    {   // 2:8
+        {3.35f, 0.38f, 0.0363f, 0.242f, 0.826f, 0.126f, 0.0768f, 0.0687f, 0.0648f},
+        {3.31f, 0.355f, 0.0644f, 0.122f, 0.408f, 0.0137f, 0.0912f, 0.0621f, 0.0409f},
+        {3.12f, 0.321f, 0.0373f, 0.131f, 0.381f, 0.0118f, 0.103f, 0.0745f, 0.0932f},
+        {2.97f, 0.267f, 0.0569f, 0.0568f, 0.195f, 0.0f, 0.0989f, 0.0787f, 0.0599f},
+        {0.497f, 0.0439f, 1.32f, 0.115f, 4.26f, 0.366f, 0.0929f, 0.0918f, 0.0405f},
+        {2.9f, 0.363f, 0.0936f, 0.072f, 0.266f, 0.0633f, 0.0f, 0.0824f, 0.0f},
+        {2.82f, 0.252f, 0.178f, 0.138f, 0.764f, 0.0494f, 0.0974f, 0.0794f, 0.0695f},
+        {2.05f, 0.0f, 0.855f, 0.101f, 1.75f, 0.0f, 0.0f, 0.13f, 0.0647f},
+        {1.85f, 0.0f, 0.606f, 0.0419f, 1.56f, 0.0f, 0.0f, 0.135f, 0.0636f},
+        {1.88f, 0.0f, 0.663f, 0.0268f, 1.6f, 0.0f, 0.0f, 0.183f, 0.00106f},
+        {2.59f, 0.14f, 0.275f, 0.0f, 0.48f, 0.0f, 0.0f, 0.0735f, 0.0562f},
+        {2.98f, 0.377f, 0.0354f, 0.293f, 1.43f, 0.126f, 0.0789f, 0.07f, 0.0698f},
+        {2.55f, 0.0f, 0.866f, 0.00615f, 2.32f, 0.0127f, 0.117f, 0.0838f, 0.0425f},
+        {3.11f, 0.3f, 0.282f, 0.0f, 0.352f, 0.0595f, 0.0943f, 0.0826f, 0.0274f},
+        {3.14f, 0.218f, 0.253f, 0.0f, 0.315f, 0.054f, 0.102f, 0.115f, 0.0922f},
+        {1.21f, 0.0967f, 1.46f, 0.0766f, 3.69f, 0.377f, 0.122f, 0.0768f, 0.0694f},
+    },
+    {   // dense
+        {3.26f, 0.27f, 0.0964f, 0.265f, 1.0f, 0.0292f, 0.0913f, 0.0827f, 0.0613f},
+        {2.97f, 0.228f, 0.111f, 0.137f, 0.354f, 0.058f, 0.0746f, 0.0696f, 0.0535f},
+        {3.2f, 0.202f, 0.139f, 0.0992f, 0.0709f, 0.0302f, 0.125f, 0.0906f, 0.0775f},
+        {2.8f, 0.248f, 0.0f, 0.159f, 0.0719f, 0.0209f, 0.0917f, 0.0874f, 0.0862f},
+        {0.789f, 0.0529f, 1.12f, 0.0897f, 4.02f, 0.197f, 0.125f, 0.0748f, 0.0835f},
+        {2.78f, 0.208f, 0.0864f, 0.115f, 0.236f, 0.0359f, 0.063f, 0.0832f, 0.0216f},
+        {2.99f, 0.219f, 0.142f, 0.246f, 0.522f, 0.0318f, 0.112f, 0.0843f, 0.0831f},
+        {2.44f, 0.0304f, 0.653f, 0.268f, 1.76f, 0.0f, 0.0f, 0.196f, 0.0796f},
+        {2.12f, 0.00182f, 0.515f, 0.0939f, 1.35f, 0.0f, 0.0f, 0.216f, 0.00446f},
+        {2.33f, 0.235f, 0.18f, 0.48f, 1.26f, 0.0f, 0.165f, 0.212f, 0.0f},
+        {1.94f, 0.0248f, 0.308f, 0.141f, 1.2f, 0.0f, 0.0f, 0.219f, 0.0f},
+        {2.93f, 0.398f, 0.0f, 0.402f, 1.32f, 0.0534f, 0.0946f, 0.0866f, 0.0729f},
+        {2.5f, 0.0f, 0.739f, 0.179f, 2.63f, 0.0558f, 0.108f, 0.0873f, 0.0404f},
+        {2.14f, 0.0f, 0.352f, 0.0184f, 1.52f, 0.0104f, 0.143f, 0.0633f, 0.0422f},
+        {1.6f, 0.0f, 0.346f, 0.0195f, 1.93f, 0.024f, 0.0885f, 0.102f, 0.0743f},
+        {1.35f, 0.0f, 1.48f, 0.0998f, 3.39f, 0.28f, 0.134f, 0.0853f, 0.0743f},
+    },
+    {   // 3:8, 4:8, 5:8
+        {3.71f, 0.314f, 0.211f, 0.2f, 0.891f, 0.00627f, 0.101f, 0.0949f, 0.061f},
+        {3.36f, 0.317f, 0.167f, 0.0885f, 0.439f, 0.0f, 0.0904f, 0.0874f, 0.0476f},
+        {3.22f, 0.302f, 0.11f, 0.122f, 0.479f, 0.00277f, 0.104f, 0.0845f, 0.0767f},
+        {2.91f, 0.248f, 0.121f, 0.0355f, 0.312f, 0.0f, 0.0575f, 0.108f, 0.0512f},
+        {1.0f, 0.151f, 1.61f, 0.0681f, 3.77f, 0.328f, 0.116f, 0.0849f, 0.0579f},
+        {2.96f, 0.394f, 0.0997f, 0.13f, 0.343f, 0.0528f, 0.0f, 0.0834f, 0.0f},
+        {3.05f, 0.218f, 0.328f, 0.108f, 0.762f, 0.0167f, 0.0965f, 0.101f, 0.0623f},
+        {2.05f, 0.0548f, 0.975f, 0.0881f, 1.92f, 0.0f, 0.0f, 0.131f, 0.0702f},
+        {1.93f, 0.0f, 0.695f, 0.0183f, 1.59f, 0.0f, 0.0f, 0.125f, 0.108f},
+        {1.9f, 0.0815f, 0.787f, 0.138f, 1.61f, 0.0f, 0.0f, 0.143f, 0.00807f},
+        {1.9f, 0.0f, 0.563f, 0.0931f, 1.19f, 0.0f, 0.0f, 0.167f, 0.0f},
+        {3.46f, 0.315f, 0.26f, 0.223f, 1.14f, 0.0f, 0.106f, 0.102f, 0.0946f},
+        {2.15f, 0.0271f, 1.12f, 0.0f, 3.11f, 0.0161f, 0.108f, 0.0891f, 0.0325f},
+        {3.08f, 0.317f, 0.316f, 0.00487f, 0.586f, 0.0176f, 0.105f, 0.0868f, 0.0532f},
+        {2.16f, 0.0174f, 0.533f, 0.0f, 1.49f, 0.029f, 0.168f, 0.0398f, 0.0818f},
+        {1.09f, 0.138f, 1.92f, 0.0f, 4.0f, 0.314f, 0.125f, 0.097f, 0.0723f},
+    },
+};
+
+static int cost_group(int kind) {
+    switch (kind) {
+        case NM_KIND_SP42: return 0;
+        case NM_KIND_C14: case NM_KIND_C18: return 1;
+        case NM_KIND_C28: return 2;
+        case NM_KIND_DENSE: return 3;
+        default: return 4;
+    }
+}
+
+int schedule_tile(int kind, int m, int n, int k, int out_mode, int planned) {
+    // 32-bit divisions only: this runs in every call
+    const uint32_t cus = (uint32_t)device_cu_count();
+    uint32_t bytes = 0, split_line = 0;   // per output element; of rows that do not start on a 128-byte line
+    for (uint32_t eb : {4u, 2u, 1u})
+        if (out_mode & (eb == 4 ? NM_OUT_I32 : eb == 2 ? NM_OUT_F16 : NM_OUT_I8)) {
+            bytes += eb;
+            if ((uint64_t)n * eb % 128 != 0) split_line += eb;
+        }
+    const float mn = (float)m * (float)n * 1e-6f, out_mb = mn * (float)bytes, split_mb = mn * (float)split_line;
+    const float x_mb = (float)m * (float)k * 1e-6f;
+    const uint32_t k_steps = ((uint32_t)k + kKStep - 1) / kKStep;
+    const CostTerms *cost = kCost[cost_group(kind)];
+    auto estimate_us = [&](int t) {
+        const CostTerms &c = cost[t];
+        const uint32_t tn = (uint32_t)kTiles[t].tile_n(), tm = (uint32_t)kTiles[t].tile_m();
+        const uint32_t tiles = (((uint32_t)n + tn - 1) / tn) * (((uint32_t)m + tm - 1) / tm);   // below 2^29
+        const float steps = (float)(kTiles[t].layout == kKSliced ? (k_steps + 3) / 4 : k_steps);
+        const float rounds = (float)((tiles + cus - 1) / cus), mean = (float)tiles / (float)cus;
+        return c.launch + steps * (c.chain + c.round_steps * rounds + c.mean_steps * mean) +
+               rounds * (c.rounds + c.round_bytes * (float)bytes) + c.out_mb * out_mb + c.split_line_mb * split_mb +
+               c.x_mb * x_mb;
+    };
+    int best = planned;
+    float least = 0.97f * estimate_us(planned);
+    for (int t = 0; t < kNumSchedules; ++t) {
+        const float us = estimate_us(t);
+        if (us < least) {
+            least = us;
+            best = t;
+        }
+    }
+    return best;
+}
+
 }  // namespace nmspmm

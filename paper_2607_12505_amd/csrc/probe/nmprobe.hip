@@ -162,6 +162,7 @@ extern "C" nm_status nm_probe_store_only(const nm_plan *plan, int m, int n, cons
     a.tiles_n = (n + p.tile_n - 1) / p.tile_n;
     a.tiles_m = (m + p.tile_m - 1) / p.tile_m;
     a.split_k = 1;
+    a.stream_out = stream_out_for(n);
     a.group_rows = 0;
     return launch_gemm(p.kind, p.tile, a, p.grid, stream) == 0 ? NM_OK : NM_ERR_HIP;
 }

@@ -1,0 +1,40 @@
+"""The schedule of a call without an explicit plan (CPU): the estimate picks a
+tile of the table for every shape, kind and output, never needs more than the
+planner's plan, and reaches each tile that only such calls run on."""
+import ctypes
+
+import numpy as np
+import pytest
+
+from paper_2607_12505_amd import nmspmm
+from schedule_cases import CASES, PATTERN, schedule_tile
+
+
+@pytest.mark.parametrize("kind", nmspmm.ALL_KINDS)
+def test_every_shape_gets_a_tile_of_the_table(kind):
+    rng = np.random.default_rng(kind)
+    for _ in range(400):
+        m, n, k = int(np.exp(rng.uniform(0, 12))), 4 * int(np.exp(rng.uniform(0, 8))), 16 * int(np.exp(rng.uniform(0, 6)))
+        mode = int(rng.integers(1, 8))
+        planned = int(rng.integers(0, nmspmm.num_tiles()))
+        tile = schedule_tile(kind, m, n, k, mode, planned)
+        assert 0 <= tile < 16
+        assert tile == schedule_tile(kind, m, n, k, mode, planned)
+
+
+@pytest.mark.parametrize("case", CASES, ids=str)
+def test_cases_reach_the_unplanned_tiles(case):
+    m, n, k, kind, mode, want = case
+    d = nmspmm.compress_size(n, k, *PATTERN[kind])
+    p = nmspmm.spmm_plan(d, m, mode)
+    assert p.expand == 0 and p.tile < nmspmm.num_tiles() and p.split_k == 1
+    assert schedule_tile(kind, m, n, k, mode, p.tile) == want
+
+
+def test_internal_tiles_are_no_plans():
+    d = nmspmm.compress_size(256, 256, 2, 4)
+    for tile in (12, 15, 16):
+        with pytest.raises(nmspmm.NmError):
+            nmspmm.spmm_plan_complete(d, 100, nmspmm.make_plan(nmspmm.NM_KIND_SP42, tile, 1))
+        with pytest.raises(nmspmm.NmError):
+            nmspmm.tile_info(tile)
