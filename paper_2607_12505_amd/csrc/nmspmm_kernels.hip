@@ -93,11 +93,17 @@ constexpr int kStoreNT = 2;
 // reserves, so it warns that the clobber below may not be honoured; the
 // generated code of these kernels uses M0 nowhere else (LDS instructions do
 // not need it on gfx950), so nothing live is overwritten.
+// The hardware needs one wait state between a scalar write of M0 and a load
+// to LDS that reads it, or the load may still see the M0 before; the compiler
+// inserts none inside a statement, so each one holds its own (an s_nop, or
+// the compare and branch).  tests/test_isa_waits.py checks the built code.
 __device__ inline void dma16(const void *g, uint32_t lds_base) {
-    asm volatile("s_mov_b32 m0, %1\n\tglobal_load_lds_dwordx4 %0, off" ::"v"(g), "s"(lds_base) : "memory", "m0");
+    asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, off" ::"v"(g), "s"(lds_base)
+                 : "memory", "m0");
 }
 __device__ inline void dma4(const void *g, uint32_t lds_base) {
-    asm volatile("s_mov_b32 m0, %1\n\tglobal_load_lds_dword %0, off" ::"v"(g), "s"(lds_base) : "memory", "m0");
+    asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dword %0, off" ::"v"(g), "s"(lds_base)
+                 : "memory", "m0");
 }
 // The same with a wave-uniform 64-bit base in SGPRs and a 32-bit per-lane
 // byte offset (no per-lane 64-bit address arithmetic), skipped unless the
@@ -105,7 +111,7 @@ __device__ inline void dma4(const void *g, uint32_t lds_base) {
 // the surrounding schedule stays one block.
 __device__ inline void dma16o_if(const void *base, uint32_t off, uint32_t lds_base, int live) {
     asm volatile(
-        "s_cmp_lt_i32 %3, 1\n\ts_cbranch_scc1 1f\n\ts_mov_b32 m0, %2\n\tglobal_load_lds_dwordx4 %0, %1\n1:" ::"v"(off),
+        "s_mov_b32 m0, %2\n\ts_cmp_lt_i32 %3, 1\n\ts_cbranch_scc1 1f\n\tglobal_load_lds_dwordx4 %0, %1\n1:" ::"v"(off),
         "s"(base), "s"(lds_base), "s"(live)
         : "m0", "scc");
 }
