@@ -251,7 +251,7 @@ nm_status nm_workspace_init(void *ws, size_t bytes, void *stream);
 /* ---------------------------------------------------------------- GEMMs */
 
 /* Sparse GEMM on a packed weight (Sec. 4.2-4.3): Y = X W^T and/or
- * Yh = fp16(fp32(Y) * scale[j]).
+ * Yh = fp16(fp32(Y) * scale[j]), the product rounded once, to binary16.
  *   X      device int8 [m x k], row-major (k = desc->k)
  *   vals   device copy of nm_compress's vals (desc->vals_bytes)
  *   meta   device copy of nm_compress's meta (desc->meta_bytes; NULL allowed
@@ -350,7 +350,8 @@ typedef struct nm_expand_job {
 
 /* Outputs of one GEMM: any non-empty subset.
  *   y       device int32 [m x n]  Y = X W^T
- *   yh      device binary16 [m x n] fp16(fp32(Y) * scale[j]), needs scale
+ *   yh      device binary16 [m x n] fp16(fp32(Y) * scale[j]), the product
+ *           rounded once (to binary16), needs scale
  *   scale   device float32 [n]
  *   yq      device int8 [m x n]  q8(fp32(Y) * qscale[j]), needs qscale
  *   qscale  device float32 [n]
