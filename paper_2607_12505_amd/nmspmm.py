@@ -312,28 +312,31 @@ def _stream(stream) -> Optional[int]:
     return raw(torch.cuda.current_device())
 
 
-class Workspace:
-    """A zero-initialised device buffer that grows on demand (one per device).
-
-    The library keeps its counters at zero after every call, so the buffer is
-    initialised once, when it is (re)allocated."""
-
-    def __init__(self):
-        self._bufs = {}
-
-    def get(self, nbytes: int, device):
-        torch = _torch()
-        if nbytes == 0:
-            return None, 0
-        key = torch.device(device).index or 0
-        buf = self._bufs.get(key)
-        if buf is None or buf.numel() < nbytes:
-            buf = torch.zeros(max(nbytes, 1 << 20), dtype=torch.uint8, device=device)
-            self._bufs[key] = buf
-        return buf, buf.numel()
+_COUNTER_BYTES = 16384   # per-tile counters at the start of a split-K workspace
 
 
-_WS = Workspace()
+def _workspace(plan: NmPlan, nbytes: int, X, stream):
+    """Workspace of one call that was given none: memory of its own from
+    torch's allocator, on the stream that the call runs on.
+
+    The allocator orders its reuse on that stream, keeps calls of other streams
+    and host threads apart, and under graph capture takes it from the memory
+    that the graph owns.  (One buffer per device would be written by two calls
+    at once, and dropped while a captured graph still holds its address.)  Only
+    split-K reads the counters, so only there are they cleared."""
+    if nbytes == 0:
+        return None, 0
+    torch = _torch()
+    if stream is None or stream.cuda_stream == _stream(None):
+        ws = X.new_empty(nbytes, dtype=torch.uint8)
+    else:
+        if not isinstance(stream, torch.cuda.Stream):
+            stream = torch.cuda.ExternalStream(stream.cuda_stream, device=X.device)
+        with torch.cuda.stream(stream):
+            ws = X.new_empty(nbytes, dtype=torch.uint8)
+    if plan.split_k > 1:
+        _check(lib().nm_workspace_init(_ptr(ws), min(nbytes, _COUNTER_BYTES), _stream(stream)), "nm_workspace_init")
+    return ws, nbytes
 
 
 @dataclasses.dataclass
@@ -409,7 +412,9 @@ def spmm(X, w: DeviceWeight, Y=None, scale=None, Yh=None, plan: Optional[NmPlan]
     """Sparse GEMM on torch device tensors.  Y (int32), Yh (float16, or int16
     view of binary16) and Yq (int8) are written in place; returns (Y, Yh), or
     (Y, Yh, Yq) when Yq is given.  Without Yq this calls nm_spmm_ex, with it
-    nm_spmm_out; with an expansion job (expand_job()) nm_spmm_out_expand."""
+    nm_spmm_out; with an expansion job (expand_job()) nm_spmm_out_expand.
+    Without ws a call that needs a workspace takes one for itself (_workspace);
+    a ws must be zero at its first use and not be shared by unordered calls."""
     torch = _torch()
     d = w.desc
     if X.dim() != 2:
@@ -426,7 +431,7 @@ def spmm(X, w: DeviceWeight, Y=None, scale=None, Yh=None, plan: Optional[NmPlan]
     p = spmm_plan_complete(w.desc, m, plan) if plan is not None else spmm_plan(w.desc, m, mode or NM_OUT_I32)
     need = workspace_size(p, m, w.desc.n)
     if ws is None:
-        ws, ws_bytes = _WS.get(need, X.device)
+        ws, ws_bytes = _workspace(p, need, X, stream)
     else:
         ws_bytes = ws.numel() * ws.element_size()
     pl = ctypes.byref(plan) if plan is not None else None
@@ -489,7 +494,7 @@ def gemm_i8_dense(X, W, Y=None, scale=None, Yh=None, plan: Optional[NmPlan] = No
     p = plan if plan is not None else dense_plan(m, n, k, mode or NM_OUT_I32)
     need = workspace_size(p, m, n)
     if ws is None:
-        ws, ws_bytes = _WS.get(need, X.device)
+        ws, ws_bytes = _workspace(p, need, X, stream)
     else:
         ws_bytes = ws.numel() * ws.element_size()
     pl = ctypes.byref(plan) if plan is not None else None
