@@ -217,7 +217,8 @@ nm_status nm_spmm_plan(const nm_desc *desc, int m, int out_mode, nm_plan *plan);
  * workspace.  Needs no GPU.  Errors: NM_ERR_ARG (bad descriptor or plan: a
  * kind other than the descriptor's, an unknown tile, split_k outside
  * {1, 2, 4, 8} or above the k-steps, expand = 1 for a kind that is not
- * compact), NM_ERR_SHAPE. */
+ * compact), NM_ERR_SHAPE (also expand = 1 where the expanded weight has 2^32
+ * bytes or more; the planners then keep expand = 0). */
 nm_status nm_spmm_plan_complete(const nm_desc *desc, int m, nm_plan *plan);
 
 /* Same as nm_spmm_plan for the dense baseline GEMM of shape (m, n, k). */

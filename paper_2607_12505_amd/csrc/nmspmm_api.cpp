@@ -100,7 +100,7 @@ nm_status run_gemm(int kind, const int8_t *X, int m, const int8_t *A, const uint
     // outputs, X and the weight are addressed with 32-bit byte offsets
     if ((int64_t)m * n >= ((int64_t)1 << 29)) return NM_ERR_SHAPE;
     if ((int64_t)m * k >= ((int64_t)1 << 32)) return NM_ERR_SHAPE;
-    if (stored_weight_bytes(kind, n, k, n_frags, k_steps) >= ((int64_t)1 << 32)) return NM_ERR_SHAPE;
+    if (stored_weight_bytes(kind, n, k, n_frags, k_steps) >= kWeightLimit) return NM_ERR_SHAPE;
     nm_plan plan;
     if (forced) {
         plan = *forced;

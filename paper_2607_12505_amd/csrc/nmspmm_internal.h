@@ -139,6 +139,8 @@ size_t workspace_bytes(const nm_plan &plan, int m, int n);   // the whole worksp
 constexpr bool kind_is_compact(int kind) { return kind != NM_KIND_SP42 && kind != NM_KIND_DENSE && kind_is_valid(kind); }
 constexpr int expanded_kind(int kind) { return kind_is_sp42(kind) ? NM_KIND_SP42 : NM_KIND_DENSE; }
 int64_t expanded_bytes(int kind, int n, int k);
+// The kernels address a weight, stored or expanded, with 32-bit byte offsets.
+constexpr int64_t kWeightLimit = (int64_t)1 << 32;
 int launch_expand(int kind, const int8_t *vals, const uint8_t *meta, int n, int k, int8_t *out, void *stream);
 // Waves per workgroup of a tile's kernel (each tail workgroup of a launch
 // that carries an expansion expands one block per wave).

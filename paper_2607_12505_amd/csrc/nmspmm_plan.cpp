@@ -76,6 +76,7 @@ nm_status complete_plan(int kind, int m, int n, int k, nm_plan *p) {
     const int k_steps = (k + kKStep - 1) / kKStep;
     p->reserved = 0;
     p->expand_bytes = p->expand ? expanded_bytes(kind, n, k) : 0;
+    if (p->expand_bytes >= kWeightLimit) return NM_ERR_SHAPE;
     bool ok_split = false;
     for (int s : kSplitSet) ok_split |= (p->split_k == s);
     if (!ok_split || p->split_k > (k_steps > 0 ? k_steps : 1)) return NM_ERR_ARG;
@@ -267,6 +268,9 @@ nm_status make_plan(int kind, int m, int n, int k, int out_mode, nm_plan *plan) 
         plan->expand = kind_is_compact(kind) && (kind != NM_KIND_C14 || (many_rows && !k_sliced)) ? 1 : 0;
     else
         plan->expand = kind_is_compact(kind) && many_rows && !k_sliced && once ? 1 : 0;
+    // a weight that fits its limit as stored may pass it expanded (twice the
+    // bytes, less the positions): then it is decoded in the kernel
+    if (plan->expand && expanded_bytes(kind, n, k) >= kWeightLimit) plan->expand = 0;
     return complete_plan(kind, m, n, k, plan);
 }
 

@@ -258,3 +258,22 @@ def test_split_k_tile_limit():
     assert nmspmm.workspace_size(p, 64 * 64, 64 * 64) == 16384 + 2 * 64 * 64 * 64 * 64 * 4
     p1 = nmspmm.make_plan(nmspmm.NM_KIND_SP42, 5, 1)
     assert nmspmm.workspace_size(p1, 64 * 64, 64 * 64) == 0
+
+
+@pytest.mark.parametrize("N,M,n,k", [(1, 4, 32768, 262144), (1, 8, 32768, 262144), (2, 8, 32768, 229376),
+                                     (3, 8, 32768, 196608), (4, 8, 32768, 196608), (5, 8, 32768, 131072)])
+def test_weights_too_large_expanded_stay_compact(N, M, n, k):
+    # the kernels read a weight with 32-bit byte offsets: one that fits as
+    # stored but not expanded is decoded in the kernel, and refused expanded
+    m = 8448
+    d = nmspmm.compress_size(n, k, N, M)
+    e, nbytes = nmspmm.expand_size(d)
+    assert d.vals_bytes + d.meta_bytes < 2 ** 32 <= nbytes
+    for mode in (nmspmm.NM_OUT_I32, nmspmm.NM_OUT_I32 | nmspmm.NM_PLAN_EXPAND_CARRIED):
+        assert nmspmm.spmm_plan(d, m, mode).expand == 0
+    with pytest.raises(nmspmm.NmError) as err:
+        nmspmm.spmm_plan_complete(d, m, nmspmm.make_plan(d.kind, 0, 1, expand=1))
+    assert err.value.status == nmspmm.NM_ERR_SHAPE
+    # just below the limit the expansion stays
+    fits = nmspmm.compress_size(n, k * (2 ** 32 - 1) // nbytes // 256 * 256, N, M)
+    assert nmspmm.expand_size(fits)[1] < 2 ** 32 and nmspmm.spmm_plan(fits, m, nmspmm.NM_OUT_I32).expand == 1
