@@ -77,6 +77,23 @@ nm_status nm_probe_mfma_layout(int kind, const int32_t *a, const int32_t *b, con
  * m == 0 writes nothing. */
 nm_status nm_probe_store_only(const nm_plan *plan, int m, int n, const nm_outputs *out, void *stream);
 
+/* Calls without a plan choose among nm_probe_num_schedule_tiles() workgroup
+ * tiles: the nm_num_tiles() that plans can name and more.  Host only:
+ *   nm_probe_schedule_tile:  the tile that such a call runs for a GEMM kernel
+ *                            of `kind` (with an expansion once per call: the
+ *                            kind that runs after it) whose plan names
+ *                            `planned`; -1 for an unknown kind or tile or a
+ *                            size below 1
+ * Device: nm_probe_spmm_tile is nm_spmm_out_expand without a plan (job may be
+ * NULL) on the tile `tile` instead of that choice, so that tests reach every
+ * kernel and timings compare them.  A dense W goes by an 8:8 descriptor.
+ * Errors: as nm_spmm_out_expand, and NM_ERR_ARG for an unknown tile. */
+int nm_probe_num_schedule_tiles(void);
+int nm_probe_schedule_tile(int kind, int m, int n, int k, int out_mode, int planned);
+nm_status nm_probe_spmm_tile(const int8_t *X, int m, const int8_t *vals, const uint8_t *meta, const nm_desc *desc,
+                             const nm_outputs *out, void *ws, size_t ws_bytes, void *stream,
+                             const nm_expand_job *job, int tile);
+
 /* Timing events (hipEvent_t behind a void pointer) created with
  * hipEventDisableSystemFence: recording one adds no system-scope memory
  * fence (no cache write-back and invalidation) when it completes, so events

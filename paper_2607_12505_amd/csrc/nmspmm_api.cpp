@@ -76,7 +76,7 @@ static nm_status check_job(const nm_expand_job *job) {
 
 nm_status run_gemm(int kind, const int8_t *X, int m, const int8_t *A, const uint8_t *meta, int n, int k,
                    int k_steps, int n_frags, const nm_outputs *out, void *ws, size_t ws_bytes, void *stream,
-                   const nm_plan *forced, WorkspaceFn ws_fn, const nm_expand_job *job) {
+                   const nm_plan *forced, WorkspaceFn ws_fn, const nm_expand_job *job, int only_tile) {
     if (m < 0) return NM_ERR_SHAPE;
     if (job) {
         nm_status st = check_job(job);
@@ -146,7 +146,7 @@ nm_status run_gemm(int kind, const int8_t *X, int m, const int8_t *A, const uint
     int grid = plan.grid;
     if (!forced && !split) {
         // the schedule is ours to choose: the planner's tile or a faster one
-        tile = schedule_tile(run_kind, m, n, k, out_mode_of(o), plan.tile);
+        tile = only_tile >= 0 ? only_tile : schedule_tile(run_kind, m, n, k, out_mode_of(o), plan.tile);
         grid = ((n + kTiles[tile].tile_n() - 1) / kTiles[tile].tile_n()) *
                ((m + kTiles[tile].tile_m() - 1) / kTiles[tile].tile_m());
     }

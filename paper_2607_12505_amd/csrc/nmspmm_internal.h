@@ -155,11 +155,12 @@ int launch_quantize_f16(const uint16_t *x, int64_t count, float inv_scale, int8_
 
 // Argument checks, planning and launch of one GEMM (nmspmm_api.cpp).  When
 // the plan needs a workspace and ws_fn is given, ws_fn supplies it instead of
-// ws / ws_bytes.
+// ws / ws_bytes.  only_tile >= 0: a call without a plan runs that tile instead
+// of the one schedule_tile chooses (for the probe library).
 typedef nm_status (*WorkspaceFn)(size_t need, void *stream, void **ws, size_t *ws_bytes);
 nm_status run_gemm(int kind, const int8_t *X, int m, const int8_t *A, const uint8_t *meta, int n, int k,
                    int k_steps, int n_frags, const nm_outputs *out, void *ws, size_t ws_bytes, void *stream,
-                   const nm_plan *forced, WorkspaceFn ws_fn, const nm_expand_job *job = nullptr);
+                   const nm_plan *forced, WorkspaceFn ws_fn, const nm_expand_job *job = nullptr, int only_tile = -1);
 nm_status check_desc(const nm_desc *d);
 int kind_of(const nm_desc *d);
 

@@ -167,6 +167,23 @@ extern "C" nm_status nm_probe_store_only(const nm_plan *plan, int m, int n, cons
     return launch_gemm(p.kind, p.tile, a, p.grid, stream) == 0 ? NM_OK : NM_ERR_HIP;
 }
 
+extern "C" int nm_probe_num_schedule_tiles(void) { return kNumSchedules; }
+
+extern "C" int nm_probe_schedule_tile(int kind, int m, int n, int k, int out_mode, int planned) {
+    if (!kind_is_valid(kind) || m < 1 || n < 1 || k < 1 || planned < 0 || planned >= kNumTiles) return -1;
+    return schedule_tile(kind, m, n, k, out_mode, planned);
+}
+
+extern "C" nm_status nm_probe_spmm_tile(const int8_t *X, int m, const int8_t *vals, const uint8_t *meta,
+                                        const nm_desc *desc, const nm_outputs *out, void *ws, size_t ws_bytes,
+                                        void *stream, const nm_expand_job *job, int tile) {
+    nm_status st = check_desc(desc);
+    if (st != NM_OK) return st;
+    if (tile < 0 || tile >= kNumSchedules) return NM_ERR_ARG;
+    return run_gemm(kind_of(desc), X, m, vals, meta, desc->n, desc->k, desc->k_steps, desc->n_frags, out, ws,
+                    ws_bytes, stream, nullptr, nullptr, job, tile);
+}
+
 // Timing events without the system-scope fence a default event performs when
 // it completes (a write-back and invalidation of the caches): between two
 // GEMMs such a fence costs microseconds and leaves the next GEMM with cold

@@ -11,13 +11,15 @@ import os
 import threading
 
 from . import nmspmm
-from .nmspmm import NM_KIND_DENSE, NM_KIND_SP42, NmOutputs, NmPlan, _check, _check_outputs, _on_device, _outputs
-from .nmspmm import _ptr, _stream, _torch
+from .nmspmm import NM_KIND_DENSE, NM_KIND_SP42, NmDesc, NmExpandJob, NmOutputs, NmPlan, _check, _check_outputs
+from .nmspmm import _need, _on_device, _out_mode, _outputs, _ptr, _stream, _torch, _workspace, spmm_plan
+from .nmspmm import workspace_size
 
 LIB_PATH = os.path.join(os.path.dirname(os.path.abspath(__file__)), "libnmprobe.so")
 
 # Every symbol include/nmprobe.h declares (checked by the CPU tests).
 EXPORTED = ("nm_probe_mfma_rate", "nm_probe_mfma_layout", "nm_wall_clock_khz", "nm_probe_store_only",
+            "nm_probe_num_schedule_tiles", "nm_probe_schedule_tile", "nm_probe_spmm_tile",
             "nm_probe_event_create", "nm_probe_event_destroy", "nm_probe_event_record", "nm_probe_event_elapsed_ms")
 NM_PROBE_WORDS = 4096
 
@@ -43,6 +45,10 @@ def lib() -> ctypes.CDLL:
             "nm_wall_clock_khz": ([ctypes.POINTER(ctypes.c_int32)], i32),
             "nm_probe_mfma_layout": ([i32, vp, vp, vp, vp, vp], i32),
             "nm_probe_store_only": ([ctypes.POINTER(NmPlan), i32, i32, ctypes.POINTER(NmOutputs), vp], i32),
+            "nm_probe_num_schedule_tiles": ([], i32),
+            "nm_probe_schedule_tile": ([i32] * 6, i32),
+            "nm_probe_spmm_tile": ([vp, i32, vp, vp, ctypes.POINTER(NmDesc), ctypes.POINTER(NmOutputs), vp,
+                                    ctypes.c_size_t, vp, ctypes.POINTER(NmExpandJob), i32], i32),
             "nm_probe_event_create": ([ctypes.POINTER(vp)], i32),
             "nm_probe_event_destroy": ([vp], i32),
             "nm_probe_event_record": ([vp, vp], i32),
@@ -100,8 +106,37 @@ def probe_store_only(plan: NmPlan, m: int, n: int, Y=None, scale=None, Yh=None, 
            "nm_probe_store_only")
 
 
+def num_schedule_tiles() -> int:
+    """nm_probe_num_schedule_tiles: workgroup tiles that calls without a plan choose among."""
+    return lib().nm_probe_num_schedule_tiles()
+
+
+def schedule_tile(kind: int, m: int, n: int, k: int, out_mode: int, planned: int) -> int:
+    """nm_probe_schedule_tile: the tile of a call without a plan (-1 for an unknown kind, tile or size)."""
+    return lib().nm_probe_schedule_tile(kind, m, n, k, out_mode, planned)
+
+
+def probe_spmm_tile(X, w, tile: int, Y=None, scale=None, Yh=None, Yq=None, qscale=None, job=None, stream=None):
+    """nm_probe_spmm_tile: spmm without a plan on the given tile."""
+    torch = _torch()
+    d = w.desc
+    m = X.shape[0]
+    _need(X, "X", (torch.int8,), (m, d.k))
+    _need(w.vals, "w.vals", (torch.int8,), numel=d.vals_bytes)
+    _need(w.meta, "w.meta", (torch.uint8,), numel=d.meta_bytes)
+    _check_outputs(torch, m, d.n, Y, scale, Yh, Yq, qscale)
+    _on_device((("X", X), ("w.vals", w.vals), ("w.meta", w.meta), ("Y", Y), ("Yh", Yh), ("Yq", Yq),
+                ("scale", scale), ("qscale", qscale)))
+    p = spmm_plan(d, m, _out_mode(Y, Yh, Yq))
+    ws, ws_bytes = _workspace(p, workspace_size(p, m, d.n), X, stream)
+    o = _outputs(Y, scale, Yh, Yq, qscale)
+    _check(lib().nm_probe_spmm_tile(_ptr(X), m, _ptr(w.vals), _ptr(w.meta) if d.meta_bytes else None,
+                                    ctypes.byref(d), ctypes.byref(o), _ptr(ws), ws_bytes, _stream(stream),
+                                    ctypes.byref(job) if job is not None else None, int(tile)), "nm_probe_spmm_tile")
+
+
 __all__ = ["EXPORTED", "NM_PROBE_WORDS", "NM_KIND_DENSE", "NM_KIND_SP42", "lib", "probe_mfma_rate",
-           "wall_clock_khz", "probe_mfma_layout", "probe_store_only"]
+           "wall_clock_khz", "probe_mfma_layout", "probe_store_only", "num_schedule_tiles", "schedule_tile", "probe_spmm_tile"]
 
 
 class TimingEvent:

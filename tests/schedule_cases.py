@@ -1,6 +1,7 @@
 """Shapes whose calls without a plan run on the tiles that no plan names, and
-the library's choice for them (an internal C++ function, called by its symbol)."""
+the library's choice for them."""
 from paper_2607_12505_amd import nmspmm
+from paper_2607_12505_amd.nmprobe import schedule_tile  # noqa: F401
 
 PATTERN = {nmspmm.NM_KIND_SP42: (2, 4), nmspmm.NM_KIND_C14: (1, 4), nmspmm.NM_KIND_C28: (2, 8),
            nmspmm.NM_KIND_MK4: (4, 8), nmspmm.NM_KIND_DENSE: (8, 8)}
@@ -24,7 +25,3 @@ CASES = [
     (5014, 3508, 128, nmspmm.NM_KIND_C28, nmspmm.NM_OUT_F16, 15),
     (5186, 3412, 128, nmspmm.NM_KIND_MK4, nmspmm.NM_OUT_F16, 15),
 ]
-
-
-def schedule_tile(kind, m, n, k, mode, planned):
-    return nmspmm.lib()._ZN6nmspmm13schedule_tileEiiiiii(kind, m, n, k, mode, planned)
