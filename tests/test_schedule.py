@@ -38,3 +38,23 @@ def test_internal_tiles_are_no_plans():
             nmspmm.spmm_plan_complete(d, 100, nmspmm.make_plan(nmspmm.NM_KIND_SP42, tile, 1))
         with pytest.raises(nmspmm.NmError):
             nmspmm.tile_info(tile)
+
+
+# reductions longer than any the estimate was fitted to, whose switch away from
+# the planner's tile cost 13-25 % (the kind is the one that runs)
+@pytest.mark.parametrize("m,n,k,kind,mode,planned", [
+    (2458, 1508, 15120, nmspmm.NM_KIND_SP42, nmspmm.NM_OUT_I32, 1),
+    (7550, 484, 6576, nmspmm.NM_KIND_SP42, nmspmm.NM_OUT_I32, 1),
+    (2604, 1416, 6240, nmspmm.NM_KIND_SP42, nmspmm.NM_OUT_I32, 1),
+    (5273, 548, 5072, nmspmm.NM_KIND_SP42, nmspmm.NM_OUT_I8, 1),
+    (1462, 788, 8848, nmspmm.NM_KIND_MK5, nmspmm.NM_OUT_I32, 3),
+    (12178, 424, 12096, nmspmm.NM_KIND_DENSE, nmspmm.NM_OUT_F16, 0),
+    (1116, 4180, 5616, nmspmm.NM_KIND_C14, nmspmm.NM_OUT_I8, 1),
+    (253, 1804, 5680, nmspmm.NM_KIND_C28, nmspmm.NM_OUT_I32, 10),
+])
+def test_small_promises_past_the_fitted_reductions_are_not_taken(m, n, k, kind, mode, planned):
+    assert schedule_tile(kind, m, n, k, mode, planned) == planned
+
+
+def test_large_promises_past_the_fitted_reductions_are_taken():
+    assert schedule_tile(nmspmm.NM_KIND_SP42, 18464, 1024, 8192, nmspmm.NM_OUT_I32, 0) == 15
