@@ -87,7 +87,8 @@ nm_status nm_probe_store_only(const nm_plan *plan, int m, int n, const nm_output
  * Device: nm_probe_spmm_tile is nm_spmm_out_expand without a plan (job may be
  * NULL) on the tile `tile` instead of that choice, so that tests reach every
  * kernel and timings compare them.  A dense W goes by an 8:8 descriptor.
- * Errors: as nm_spmm_out_expand, and NM_ERR_ARG for an unknown tile. */
+ * Errors: as nm_spmm_out_expand, and NM_ERR_ARG for an unknown tile or one
+ * that is not built for the weight's kind. */
 int nm_probe_num_schedule_tiles(void);
 int nm_probe_schedule_tile(int kind, int m, int n, int k, int out_mode, int planned);
 nm_status nm_probe_spmm_tile(const int8_t *X, int m, const int8_t *vals, const uint8_t *meta, const nm_desc *desc,

@@ -146,6 +146,7 @@ nm_status run_gemm(int kind, const int8_t *X, int m, const int8_t *A, const uint
     int grid = plan.grid;
     if (!forced && !split) {
         // the schedule is ours to choose: the planner's tile or a faster one
+        if (only_tile >= 0 && !tile_built(run_kind, only_tile)) return NM_ERR_ARG;
         tile = only_tile >= 0 ? only_tile : schedule_tile(run_kind, m, n, k, out_mode_of(o), plan.tile);
         grid = ((n + kTiles[tile].tile_n() - 1) / kTiles[tile].tile_n()) *
                ((m + kTiles[tile].tile_m() - 1) / kTiles[tile].tile_m());

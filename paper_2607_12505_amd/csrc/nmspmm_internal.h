@@ -75,6 +75,12 @@ constexpr TileCfg kTiles[] = {
 };
 constexpr int kNumSchedules = sizeof(kTiles) / sizeof(kTiles[0]);
 constexpr int kNumTiles = 12;    // tiles of explicit plans: the first of the table
+// The kinds that a tile is built for: every kind for the tiles that plans can
+// name; 13 and 14 for those that schedule_tile chose them for in a million
+// random calls (m 1..500000, n and k to 20000).
+constexpr bool tile_built(int kind, int tile) {
+    return tile == 13 ? kind == NM_KIND_SP42 || kind == NM_KIND_DENSE : tile != 14 || layout_mask_values(kind) == 0;
+}
 constexpr size_t kLdsPerCu = 160 * 1024;
 
 // Everything a GEMM kernel needs; passed by value as the kernel argument.

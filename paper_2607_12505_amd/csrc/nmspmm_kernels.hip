@@ -1379,7 +1379,8 @@ int launch_one(const GemmArgs &args, int grid, void *stream) {
 template <int KIND, int T = 0>
 int launch_kind(int tile, const GemmArgs &args, int grid, void *stream) {
     if constexpr (T < kNumSchedules) {
-        if (tile == T) return launch_one<KIND, T>(args, grid, stream);
+        if constexpr (tile_built(KIND, T))
+            if (tile == T) return launch_one<KIND, T>(args, grid, stream);
         return launch_kind<KIND, T + 1>(tile, args, grid, stream);
     }
     return (int)hipErrorInvalidValue;

@@ -431,6 +431,7 @@ int schedule_tile(int kind, int m, int n, int k, int out_mode, int planned) {
     int best = planned;
     float least = (k > kFittedK ? 0.88f : 0.97f) * estimate_us(planned);
     for (int t = 0; t < kNumSchedules; ++t) {
+        if (!tile_built(kind, t)) continue;
         const float us = estimate_us(t);
         if (us < least) {
             least = us;
