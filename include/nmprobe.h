@@ -66,7 +66,7 @@ nm_status nm_probe_mfma_layout(int kind, const int32_t *a, const int32_t *b, con
  * instructions), so every output element is written with the value of an
  * empty sum (int32 0; fp16 and int8 of 0 times the scale, 0 for finite
  * scales) through the same epilogue, store pattern and cache policy as
- * nm_spmm_out.  Timing it beside the real call
+ * nm_spmm_out with one k-step.  Timing it beside the real call
  * gives the ceiling the GEMM's own stores set.  plan: a plan of an
  * output-split tile layout (the layouts nm_tile_info reports for k_gemm) with
  * split_k == 1, for the plan's kind; out: as for nm_spmm_out (device buffers,
@@ -84,6 +84,9 @@ nm_status nm_probe_store_only(const nm_plan *plan, int m, int n, const nm_output
  *                            kind that runs after it) whose plan names
  *                            `planned`; -1 for an unknown kind or tile or a
  *                            size below 1
+ *   nm_probe_stream_out:     which outputs of an output-split tile are stored
+ *                            non-temporally: their bytes per element (1, 2,
+ *                            4), or-ed; -1 for a size below 1
  * Device: nm_probe_spmm_tile is nm_spmm_out_expand without a plan (job may be
  * NULL) on the tile `tile` instead of that choice, so that tests reach every
  * kernel and timings compare them.  A dense W goes by an 8:8 descriptor.
@@ -91,6 +94,7 @@ nm_status nm_probe_store_only(const nm_plan *plan, int m, int n, const nm_output
  * that is not built for the weight's kind. */
 int nm_probe_num_schedule_tiles(void);
 int nm_probe_schedule_tile(int kind, int m, int n, int k, int out_mode, int planned);
+int nm_probe_stream_out(int m, int n, int k);
 nm_status nm_probe_spmm_tile(const int8_t *X, int m, const int8_t *vals, const uint8_t *meta, const nm_desc *desc,
                              const nm_outputs *out, void *ws, size_t ws_bytes, void *stream,
                              const nm_expand_job *job, int tile);

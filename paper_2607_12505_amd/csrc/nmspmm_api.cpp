@@ -170,7 +170,7 @@ nm_status run_gemm(int kind, const int8_t *X, int m, const int8_t *A, const uint
     a.tiles_n = (n + kTiles[tile].tile_n() - 1) / kTiles[tile].tile_n();
     a.tiles_m = (m + kTiles[tile].tile_m() - 1) / kTiles[tile].tile_m();
     a.split_k = plan.split_k;
-    a.stream_out = stream_out_for(n);
+    a.stream_out = stream_out_for(m, n, k);
     a.group_rows = group_rows_for(a.tiles_m, kTiles[tile].tile_m());
     a.gemm_grid = grid;
     if (job) {

@@ -111,17 +111,25 @@ struct GemmArgs {
     int x_n = 0, x_k = 0, x_blocks = 0, x_k_steps = 0;
 };
 
-// Store policy of each output: non-temporal where its rows start on a 128-byte
-// line, so that every store of a tile's row writes whole lines.  Where they do
-// not, a line at the border of two tiles is written in two pieces, which L2
-// can join only if the stores go through it as usual: m 14691, n 1444, k 176
-// int32 + fp16 51.8 us non-temporal and 33.3 through L2 (87 at 4 bytes a lane),
-// m 30000, n 500, k 256 int32 20.7 and 15.1; on whole lines it is the other
-// way round (m 100352, n 512, k 128 int32 35.8 and 43).
-inline int stream_out_for(int n) {
+// Store policy of each output of k_gemm: non-temporal where its rows start on
+// a 128-byte line, so that every store of a tile's row writes whole lines.
+// Where they do not, a line at the border of two tiles is written in two
+// pieces, which L2 can join only if the stores go through it as usual: m 14691,
+// n 1444, k 176 int32 + fp16 51.8 us non-temporal and 33.3 through L2 (87 at 4
+// bytes a lane), m 30000, n 500, k 256 int32 20.7 and 15.1; on whole lines it
+// is the other way round (m 100352, n 512, k 128 int32 35.8 and 43).
+// int32 rows off the lines are stored non-temporally all the same where the
+// reduction is long: the matrix work then covers the stores, and through L2
+// they would push out the operands.  664 int32 shapes timed both ways: from 12
+// k-steps on non-temporal takes 0.955 of the time (m 44423, n 2152, k 2048,
+// 4:8: 204 us against 262), below 7 1.10 (m 57962, n 2452, k 400, dense: 280
+// against 213); from 7 to 11 it is 0.936 for outputs past the 256 MB last-level
+// cache and no gain (1.003) for smaller ones.
+inline int stream_out_for(int m, int n, int k) {
     int mask = 0;
     for (int eb : {1, 2, 4})
         if ((int64_t)n * eb % 128 == 0) mask |= eb;
+    if (k > 11 * kKStep || (k > 6 * kKStep && (int64_t)m * n * 4 > ((int64_t)256 << 20))) mask |= 4;
     return mask;
 }
 

@@ -162,7 +162,7 @@ extern "C" nm_status nm_probe_store_only(const nm_plan *plan, int m, int n, cons
     a.tiles_n = (n + p.tile_n - 1) / p.tile_n;
     a.tiles_m = (m + p.tile_m - 1) / p.tile_m;
     a.split_k = 1;
-    a.stream_out = stream_out_for(n);
+    a.stream_out = stream_out_for(m, n, a.k);
     a.group_rows = 0;
     return launch_gemm(p.kind, p.tile, a, p.grid, stream) == 0 ? NM_OK : NM_ERR_HIP;
 }
@@ -173,6 +173,8 @@ extern "C" int nm_probe_schedule_tile(int kind, int m, int n, int k, int out_mod
     if (!kind_is_valid(kind) || m < 1 || n < 1 || k < 1 || planned < 0 || planned >= kNumTiles) return -1;
     return schedule_tile(kind, m, n, k, out_mode, planned);
 }
+
+extern "C" int nm_probe_stream_out(int m, int n, int k) { return m < 1 || n < 1 || k < 1 ? -1 : stream_out_for(m, n, k); }
 
 extern "C" nm_status nm_probe_spmm_tile(const int8_t *X, int m, const int8_t *vals, const uint8_t *meta,
                                         const nm_desc *desc, const nm_outputs *out, void *ws, size_t ws_bytes,

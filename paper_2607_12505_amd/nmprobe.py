@@ -19,7 +19,8 @@ LIB_PATH = os.path.join(os.path.dirname(os.path.abspath(__file__)), "libnmprobe.
 
 # Every symbol include/nmprobe.h declares (checked by the CPU tests).
 EXPORTED = ("nm_probe_mfma_rate", "nm_probe_mfma_layout", "nm_wall_clock_khz", "nm_probe_store_only",
-            "nm_probe_num_schedule_tiles", "nm_probe_schedule_tile", "nm_probe_spmm_tile",
+            "nm_probe_num_schedule_tiles", "nm_probe_schedule_tile", "nm_probe_stream_out",
+            "nm_probe_spmm_tile",
             "nm_probe_event_create", "nm_probe_event_destroy", "nm_probe_event_record", "nm_probe_event_elapsed_ms")
 NM_PROBE_WORDS = 4096
 
@@ -47,6 +48,7 @@ def lib() -> ctypes.CDLL:
             "nm_probe_store_only": ([ctypes.POINTER(NmPlan), i32, i32, ctypes.POINTER(NmOutputs), vp], i32),
             "nm_probe_num_schedule_tiles": ([], i32),
             "nm_probe_schedule_tile": ([i32] * 6, i32),
+            "nm_probe_stream_out": ([i32] * 3, i32),
             "nm_probe_spmm_tile": ([vp, i32, vp, vp, ctypes.POINTER(NmDesc), ctypes.POINTER(NmOutputs), vp,
                                     ctypes.c_size_t, vp, ctypes.POINTER(NmExpandJob), i32], i32),
             "nm_probe_event_create": ([ctypes.POINTER(vp)], i32),
@@ -116,6 +118,11 @@ def schedule_tile(kind: int, m: int, n: int, k: int, out_mode: int, planned: int
     return lib().nm_probe_schedule_tile(kind, m, n, k, out_mode, planned)
 
 
+def stream_out(m: int, n: int, k: int) -> int:
+    """nm_probe_stream_out: bytes per element, or-ed, of the outputs stored non-temporally (-1 for a size below 1)."""
+    return lib().nm_probe_stream_out(m, n, k)
+
+
 def probe_spmm_tile(X, w, tile: int, Y=None, scale=None, Yh=None, Yq=None, qscale=None, job=None, stream=None):
     """nm_probe_spmm_tile: spmm without a plan on the given tile."""
     torch = _torch()
@@ -136,7 +143,8 @@ def probe_spmm_tile(X, w, tile: int, Y=None, scale=None, Yh=None, Yq=None, qscal
 
 
 __all__ = ["EXPORTED", "NM_PROBE_WORDS", "NM_KIND_DENSE", "NM_KIND_SP42", "lib", "probe_mfma_rate",
-           "wall_clock_khz", "probe_mfma_layout", "probe_store_only", "num_schedule_tiles", "schedule_tile", "probe_spmm_tile"]
+           "wall_clock_khz", "probe_mfma_layout", "probe_store_only", "num_schedule_tiles", "schedule_tile", "stream_out",
+           "probe_spmm_tile"]
 
 
 class TimingEvent:

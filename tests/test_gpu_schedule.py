@@ -79,9 +79,9 @@ def _run_all_outputs(m, n, k, N, M, call, nthreads=1):
 
 
 # more k-steps than any ring holds (every slot refilled, several times), whole
-# and ragged reductions, rows of outputs on and off 128-byte lines, partial
-# last tiles both ways
-@pytest.mark.parametrize("n,k", [(524, 1040), (512, 1152)])
+# and ragged reductions, rows of outputs on and off 128-byte lines (the last k
+# with int32 alone stored non-temporally), partial last tiles both ways
+@pytest.mark.parametrize("n,k", [(524, 1040), (512, 1152), (524, 1424)])
 @pytest.mark.parametrize("pattern", ALL_PATTERNS, ids=str)
 @pytest.mark.parametrize("tile", range(12, 16))
 def test_every_kind_on_the_unplanned_tiles(tile, pattern, n, k):

@@ -7,6 +7,7 @@ import numpy as np
 import pytest
 
 from paper_2607_12505_amd import nmspmm
+from paper_2607_12505_amd.nmprobe import stream_out
 from schedule_cases import CASES, PATTERN, schedule_tile
 
 
@@ -60,3 +61,16 @@ def test_small_promises_past_the_fitted_reductions_are_not_taken(m, n, k, kind, 
 
 def test_large_promises_past_the_fitted_reductions_are_taken():
     assert schedule_tile(nmspmm.NM_KIND_SP42, 18464, 1024, 8192, nmspmm.NM_OUT_I32, 0) == 15
+
+
+def test_store_policy_of_rows_on_and_off_the_lines():
+    # rows on 128-byte lines: non-temporal whatever the reduction
+    assert stream_out(100352, 512, 128) == stream_out(1000, 512, 4096) == 7
+    assert stream_out(1000, 64, 128) == 6 and stream_out(1000, 32, 128) == 4
+    # off the lines: through L2, but int32 of a long reduction as before the rows went through L2 at all
+    assert stream_out(30000, 500, 256) == 0
+    assert stream_out(44423, 2152, 2048) == 4
+    assert [stream_out(30000, 500, k) for k in (768, 1408, 1424)] == [0, 0, 4]
+    # ... from 7 k-steps where the output passes 256 MB
+    assert [stream_out(140000, 500, k) for k in (768, 784)] == [0, 4]
+    assert [stream_out(m, 500, 1024) for m in (134217, 134218)] == [0, 4]
