@@ -8,7 +8,8 @@ PATTERN = {nmspmm.NM_KIND_SP42: (2, 4), nmspmm.NM_KIND_C14: (1, 4), nmspmm.NM_KI
 
 # (m, n, k, kind, outputs, tile): ragged tokens, channels that are no multiple
 # of 16 (a partial last fragment and 16-byte chunk), reductions that are no
-# multiple of 128, one or two k-steps (less than the ring) and more
+# multiple of 128; one to three k-steps on the wide tiles (test_gpu_schedule.py
+# runs every tile past its ring), up to twelve on the others
 CASES = [
     (3674, 2524, 128, nmspmm.NM_KIND_SP42, nmspmm.NM_OUT_I8, 12),
     (4142, 1996, 144, nmspmm.NM_KIND_SP42, nmspmm.NM_OUT_F16, 12),

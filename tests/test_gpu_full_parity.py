@@ -1,6 +1,7 @@
 """Element-by-element GPU parity of every GEMM of the five benchmark
-workloads at full size, in the planner's own launch configuration (the one
-bench.py times), against the oracle's plain product run on the host threads:
+workloads at full size, against the oracle's plain product run on the host
+threads: with the planner's plan, and, where the library runs another tile
+without a plan, that call too:
 
 * int32 outputs bit-exact everywhere;
 * the fp16 dequantisation output of the DeiT-Small workload within
@@ -17,7 +18,7 @@ import numpy as np
 import pytest
 
 import oracle
-from paper_2607_12505_amd import nmspmm
+from paper_2607_12505_amd import nmprobe, nmspmm
 from paper_2607_12505_amd import workloads as wl
 import gpu_util as gu
 
@@ -47,12 +48,23 @@ def test_workload_gemm_full(cfg, idx, baseline):
     want_f16 = w.out_f16
     kind = "dense baseline" if baseline or g.N == g.M else f"{g.N}:{g.M}"
     print(f"cfg{cfg} {g.name} m={g.m} k={g.k} n={g.n} {kind}", flush=True)
-    if baseline or g.N == g.M:
-        Y, Yh = gu.run_dense(X, W, scale, want_i32=True, want_f16=want_f16)
+    mode = nmspmm.NM_OUT_I32 | (nmspmm.NM_OUT_F16 if want_f16 else 0)
+    dense = baseline or g.N == g.M
+    if dense:
+        plan, ran = nmspmm.dense_plan(g.m, g.n, g.k, mode), nmspmm.NM_KIND_DENSE
     else:
-        Y, Yh = gu.run_sparse(X, nmspmm.compress(W, g.N, g.M), scale, want_i32=True, want_f16=want_f16)
+        packed = nmspmm.compress(W, g.N, g.M)
+        plan = nmspmm.spmm_plan(packed.desc, g.m, mode)
+        ran = nmspmm.expand_size(packed.desc)[0].kind if plan.expand else plan.kind
+    tile = nmprobe.schedule_tile(ran, g.m, g.n, g.k, mode, plan.tile)
     ref = oracle.matmul_i8(X, W, nthreads=THREADS)
-    bad = np.flatnonzero(Y != ref)
-    assert bad.size == 0, f"{bad.size} int32 mismatches of {ref.size}, first at {np.unravel_index(bad[:5], ref.shape)}"
-    if want_f16:
-        gu.assert_f16_close(Yh, oracle.dequant_f16(ref, scale))
+    for p in [plan] if tile == plan.tile else [plan, None]:
+        if dense:
+            Y, Yh = gu.run_dense(X, W, scale, want_i32=True, want_f16=want_f16, plan=p)
+        else:
+            Y, Yh = gu.run_sparse(X, packed, scale, want_i32=True, want_f16=want_f16, plan=p)
+        bad = np.flatnonzero(Y != ref)
+        assert bad.size == 0, (f"tile {tile if p is None else plan.tile}: {bad.size} int32 mismatches of {ref.size}, "
+                               f"first at {np.unravel_index(bad[:5], ref.shape)}")
+        if want_f16:
+            gu.assert_f16_close(Yh, oracle.dequant_f16(ref, scale))

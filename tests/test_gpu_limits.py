@@ -1,4 +1,4 @@
-"""The largest shapes the C ABI accepts, through the planner's own launch:
+"""The largest shapes the C ABI accepts, in calls without a plan:
 outputs of just under 2^29 elements and X of just under 2^32 bytes (the
 kernels address outputs, X and the weight with 32-bit offsets).  Every output
 is prefilled with a sentinel and followed by a guard band; the oracle checks

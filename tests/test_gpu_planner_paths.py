@@ -2,11 +2,12 @@
 4.3): one seeded shape per rule, for 2:4 (stored 4:2 operand), 1:4, 1:8 and
 2:8 (compact, expanded to the 4:2 operand), 4:8 (mask layout expanded to a
 dense tile) and dense weights, compared element by element with the oracle in the launch
-configuration the planner picks (int32 and fp16 outputs, guard bands after
-both).  The expected tile of each case documents the rule it exercises;
-launches with 32 or more rows of tiles walk them in groups of 16 rows,
-including a ragged last group, also with the reduction split across
-workgroups."""
+configuration the planner picks, given to the call as its plan, and again
+without a plan, where the library may run another tile (int32 and fp16
+outputs, guard bands after both).  The expected tile of each case documents the
+rule it exercises; launches with many rows of tiles walk them in groups (16
+rows of 128 tokens or fewer), including a ragged last group, also with the
+reduction split across workgroups."""
 import numpy as np
 import pytest
 
@@ -47,7 +48,7 @@ CASES = [
     (4096, 4096, 512, "mk", (128, 128), False),   # ... shorter reduction: 128 x 128 on 8 waves
     (16500, 1024, 1024, "dn", (128, 160), False),  # ... narrow outputs, 8+ k-steps: 160 tokens (ragged rows)
     (16500, 1024, 1024, "mk", (128, 160), False),  # ... the same for 4:8, expanded once
-    # 32 or more rows of tiles: tiles walked in groups of 16 rows
+    # 32 or more rows of tiles of up to 128 tokens: walked in groups of 16 rows
     (8300, 3072, 2048, "sp", (128, 128), False),  # 65 tile rows: the last group has one row
     (5000, 1024, 512, "sp", (64, 64), False),     # 79 tile rows: the last group has 15
     (8192, 3072, 1024, "mk", (128, 128), False),
@@ -83,13 +84,15 @@ def test_planner_branch_matches_oracle(m, n, k, kind, tile, ks):
         plan = nmspmm.spmm_plan(packed.desc, m, nmspmm.NM_OUT_I32 | nmspmm.NM_OUT_F16)
     name = nmspmm.plan_kernel_name(plan)
     assert (plan.tile_n, plan.tile_m) == tile and (KS in name) == ks, name
-    if kind == "dn":
-        Y, Yh = gu.run_dense(X, W, scale, want_i32=True, want_f16=True)
-    else:
-        Y, Yh = gu.run_sparse(X, packed, scale, want_i32=True, want_f16=True)
     ref = oracle.matmul_i8(X, W)
-    assert np.array_equal(Y, ref), name
-    gu.assert_f16_close(Yh, oracle.dequant_f16(ref, scale))
+    ref_h = oracle.dequant_f16(ref, scale)
+    for p in (plan, None):
+        if kind == "dn":
+            Y, Yh = gu.run_dense(X, W, scale, want_i32=True, want_f16=True, plan=p)
+        else:
+            Y, Yh = gu.run_sparse(X, packed, scale, want_i32=True, want_f16=True, plan=p)
+        assert np.array_equal(Y, ref), name if p is not None else "without a plan"
+        gu.assert_f16_close(Yh, ref_h)
 
 
 @pytest.mark.parametrize("split", [2, 4])
