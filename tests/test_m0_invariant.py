@@ -2,8 +2,10 @@
 the compiler reserves M0 and warns that such a clobber may not be honoured.
 That is safe only while the compiled kernels use M0 for nothing else.  This
 test compiles the kernel source to gfx950 assembly (CPU only, no GPU) and
-checks that every M0 reference is one of those writes, each followed at once
-by the direct-to-LDS load that consumes it."""
+checks that every M0 reference is one of those writes, each followed by the
+direct-to-LDS load that consumes it, with nothing in between but what fills the
+wait state that the load needs after the write: an s_nop, or the compare and
+branch that may skip the load."""
 import os
 import re
 import shutil
@@ -40,6 +42,11 @@ def test_m0_is_written_only_for_direct_to_lds_loads(tmp_path):
         if not re.search(r"\bm0\b", s):
             continue
         assert re.fullmatch(r"s_mov_b32 m0, s\d+", s), f"M0 used outside the direct-to-LDS helpers: {s}"
-        assert re.match(r"global_load_lds_dword(x4)?\b", lines[i + 1]), f"M0 write not followed by its load: {s}"
+        filler = 1 if lines[i + 1] == "s_nop 0" else 2
+        if filler == 2:
+            assert re.match(r"s_cmp_lt_i32 s\d+, 1$", lines[i + 1]), f"no wait state after: {s}; {lines[i + 1]}"
+            assert re.match(r"s_cbranch_scc1 ", lines[i + 2]), f"no wait state after: {s}; {lines[i + 2]}"
+        load = lines[i + 1 + filler]
+        assert re.match(r"global_load_lds_dword(x4)?\b", load), f"M0 write not followed by its load: {s}; {load}"
         writes += 1
     assert writes > 0
