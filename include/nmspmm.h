@@ -144,7 +144,8 @@ typedef struct nm_desc {
  * then reads (expand = 1): the first costs the expansion once per row of
  * output tiles, the second once per call plus a launch.  Plans come from the
  * planners below; callers may also build one from nm_tile_info to force a
- * schedule.  Every valid plan gives bit-identical results.
+ * schedule.  A call without a plan may run another tile than its planner's plan
+ * names (see nm_spmm_ex).  Every valid plan gives bit-identical results.
  */
 typedef struct nm_plan {
     int32_t kind;          /* NM_KIND_* (the weight's kind) */
@@ -195,11 +196,13 @@ nm_status nm_decompress(const nm_desc *desc, const int8_t *vals, const uint8_t *
 
 /* ---------------------------------------------------------------- planning */
 
-/* Number of workgroup tiles the kernels are built for, and their sizes. */
+/* Number of workgroup tiles that a plan can name, and their sizes (calls
+ * without a plan choose among these and a few more). */
 int nm_num_tiles(void);
 nm_status nm_tile_info(int tile, int *tile_n, int *tile_m);
 
-/* Planner for nm_spmm (Sec. 4.3): picks tile and split_k from
+/* Planner (Sec. 4.3): the plan of its rules, and the workspace that a call
+ * without a plan needs.  Picks tile and split_k from
  * (m, n, k, pattern) so that small-token shapes still occupy every compute
  * unit, with split_k from {1, 2, 4, 8}, k-splits on 128-wide k-step
  * boundaries and at least two k-steps per split.  Needs no GPU: without one
@@ -227,8 +230,9 @@ nm_status nm_gemm_i8_dense_plan(int m, int n, int k, int out_mode, nm_plan *plan
 /* Writes into buf (NUL-terminated, at most len bytes) the name of the GEMM
  * kernel template instance a plan launches, e.g. "k_gemm<1, 2, 2, 4, 4, 3>",
  * as it appears in profiler traces (with expand = 1: the 4:2-operand or dense
- * kernel that follows the expansion kernel "k_expand<kind>").  For profiling
- * tools; needs no GPU.
+ * kernel that follows the expansion kernel "k_expand<kind>").  A call without
+ * a plan may launch the instance of another tile.  For profiling tools; needs
+ * no GPU.
  * Errors: NM_ERR_ARG (bad plan, NULL buf, len too small). */
 nm_status nm_plan_kernel_name(const nm_plan *plan, char *buf, int len);
 
@@ -374,16 +378,16 @@ nm_status nm_spmm_out(const int8_t *X, int m, const int8_t *vals, const uint8_t 
 
 /* nm_spmm_out without a caller workspace, for callers that cannot allocate
  * device memory (code under HIP graph capture, tight serving loops, harnesses
- * that forbid hipMalloc).  A plan that needs a workspace (split_k > 1) uses a
- * scratch array that the library holds in device memory instead: the 16384-byte
- * counter block plus 32 MiB (33570816 bytes in all), one copy per device, kept
- * until the process ends.  The call itself allocates nothing.  The first call
+ * that forbid hipMalloc).  A plan that needs a workspace (split_k > 1 or
+ * expand = 1) uses a scratch array that the library holds in device memory
+ * instead: the 16384-byte counter block plus 32 MiB (33570816 bytes in all),
+ * one copy per device, kept until the process ends.  The call itself allocates nothing.  The first call
  * on a device looks the array up and clears its counters with a kernel on
  * `stream`; every call leaves them at zero again.  All calls on one device
  * share that array, so calls that may overlap on one device (other streams,
  * other host threads without ordering) race on it and must not be issued.
- * Arguments as nm_spmm_out without ws / ws_bytes; plan may be NULL (the
- * planner's).  Errors as nm_spmm_out; NM_ERR_WORKSPACE when the plan needs
+ * Arguments as nm_spmm_out without ws / ws_bytes; plan may be NULL (as for
+ * nm_spmm_ex).  Errors as nm_spmm_out; NM_ERR_WORKSPACE when the plan needs
  * more than the array holds (nm_workspace_size() > 33570816), NM_ERR_HIP when
  * the array cannot be looked up. */
 nm_status nm_spmm_noalloc(const int8_t *X, int m, const int8_t *vals, const uint8_t *meta,

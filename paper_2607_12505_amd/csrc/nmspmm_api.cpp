@@ -31,16 +31,16 @@ nm_outputs outputs_of(int32_t *Y, const float *scale, uint16_t *Yh) {
 // HBM -- as it does inside a network's sequence of layers, where the layers
 // before have streamed far more than the last-level cache holds -- all of
 // them wait on the same few rows, one k-step at a time.  Walking groups of 16
-// tile rows column by column puts 16 distinct rows of X in flight per XCD
+// tile rows (of 128 tokens) column by column puts 16 distinct rows of X in flight per XCD
 // (2 MB of X and a few column tiles of the weight stay in its 4 MB L2).  Timed
 // with a 75 MB read before every launch (ViT-L/16-384 batch 32, m = 18464):
 // 2:4 fc1 on 128 x 128 tiles 125 -> 82-86 us, qkv 93 -> 65-68, fc2 84 -> 77-79,
-// proj 36 -> 32; groups of 4 or 8 rows gained less, 32 lost.  Launches with
-// fewer than 32 rows of tiles keep the row order.
-// The wider tiles keep about the same number of tokens per group (X is read
-// once per group and XCD): 256 x 256, ViT-L qkv 2:4 fp16 54.4 us in groups of
-// 16 and 52.7-53.9 in groups of 2 to 6; 256 x 160, DeiT-B batch 128 fc2 44.4
-// and 42.3.
+// proj 36 -> 32; groups of 4 or 8 rows gained less, 32 lost.  Taller tiles, one
+// or two to a CU, take smaller groups, 6 of 160 tokens and 4 of 256 or 320
+// (plans that name those tiles too): 256 x 256, ViT-L qkv 2:4 fp16 54.4 us in
+// groups of 16 and 52.7-53.9 in groups of 2 to 6; 256 x 160, DeiT-B batch 128
+// fc2 44.4 and 42.3.  Launches with fewer rows of tiles than two groups keep
+// the row order.
 int group_size(int tile_m) { return tile_m >= 256 ? 4 : tile_m >= 160 ? 6 : 16; }
 
 int64_t stored_weight_bytes(int kind, int n, int k, int n_frags, int k_steps) {

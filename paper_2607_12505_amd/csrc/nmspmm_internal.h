@@ -52,8 +52,8 @@ struct TileCfg {
     constexpr int tile_m() const { return wm * fm * 16; }
 };
 
-// Tiles the kernels are instantiated for: the candidates of the planner
-// (each is its choice for some class of shapes).
+// Tiles the kernels are instantiated for: first those that plans can name (the
+// planner's rules choose among them), then those of calls without a plan.
 constexpr TileCfg kTiles[] = {
     {2, 2, 4, 4, 2, kOutSplit},  // 0: 128 ch x 128 tok, 2-slot ring (3 workgroups per CU)
     {2, 2, 4, 2, 2, kOutSplit},  // 1: 128 ch x  64 tok, 2-slot ring

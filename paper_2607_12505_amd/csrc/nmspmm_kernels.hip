@@ -81,11 +81,15 @@ __device__ inline void tile_order(int lid, int tiles_n, int rows, int group_rows
 // that makes a buffer access coherent at agent scope (sc1).
 constexpr int kBufferFlags = 0x00020000;
 constexpr int kSc1 = 16;
-// Cache policy of the output stores: non-temporal.  Timed inside whole
+// Cache policy of streamed output stores: non-temporal.  Timed inside whole
 // workload steps (every GEMM's buffers evicted by the others' traffic before
 // it runs again), streaming the outputs past L2 and the last-level cache beat
 // the default and the device-scope (sc1) policies on every workload, by up to
-// a third on outputs larger than the 256 MB last-level cache.
+// a third on outputs larger than the 256 MB last-level cache.  Those outputs
+// all have rows that start on 128-byte lines; off the lines k_gemm stores
+// through L2 for short reductions (stream_out_for).  emit_out, the end of the
+// k-sliced tiles and of split-K merges, always streams: the choice was not
+// measured for their small outputs.
 constexpr int kStoreNT = 2;
 
 // Direct-to-LDS loads: lane L's bytes land at lds_base + L * size.  lds_base
