@@ -174,25 +174,24 @@ struct EpiScale {
 typedef unsigned int v2u __attribute__((ext_vector_type(2)));
 typedef unsigned int v4u __attribute__((ext_vector_type(4)));
 
-// The product rounded once to binary16, in the low half of the result (the
-// instruction leaves the high half alone).  Adding -0 keeps the sign of a zero
-// product.  Left to the compiler, some products were rounded to binary32 first
-// and some were not, so plans differed by a code in about 50 000.
-__device__ inline uint32_t mul_f16(float v, float s) {
-    uint32_t h;
-    asm("v_fma_mixlo_f16 %0, %1, %2, neg(0)" : "=v"(h) : "v"(v), "v"(s));
-    return h;
+// Two products, each rounded once to binary16, as one dword.  Adding -0 keeps
+// the sign of a zero product.  The s_nop is the wait state that a vector
+// instruction needs before it reads a result written to a high half; the
+// compiler adds none after a statement.  Left to the compiler, two products of
+// four are rounded to binary32 first (v_cvt_pk_f16_f32), a code off in about
+// 20 000 outputs and not the same ones on every plan.  It costs 0.2-0.7 % of a
+// GEMM whose outputs are all fp16 (m 9410, n 4064, k 256, 5:8: 33.6 -> 33.8 us);
+// a permute per pair instead of the high-half write 0.6-1.1 % (34.0).
+__device__ inline uint32_t mul2_f16(float a, float sa, float b, float sb) {
+    asm("v_fma_mixlo_f16 %0, %0, %1, neg(0)\n\tv_fma_mixhi_f16 %0, %2, %3, neg(0)\n\ts_nop 0"
+        : "+&v"(a)
+        : "v"(sa), "v"(b), "v"(sb));
+    return __builtin_bit_cast(uint32_t, a);
 }
 
-// 4 channels of one token as binary16 and as int8 codes (whose product is
-// rounded to binary32 first).
+// 4 channels of one token as binary16.
 __device__ inline v2u pack_f16(const v4i &v, const v4f &sc) {
-    v2u h;
-#pragma unroll
-    for (int q = 0; q < 2; ++q)
-        h[q] = __builtin_amdgcn_perm(mul_f16((float)v[2 * q + 1], sc[2 * q + 1]), mul_f16((float)v[2 * q], sc[2 * q]),
-                                     0x05040100u);
-    return h;
+    return v2u{mul2_f16((float)v[0], sc[0], (float)v[1], sc[1]), mul2_f16((float)v[2], sc[2], (float)v[3], sc[3])};
 }
 __device__ inline uint32_t pack_q8(const v4i &v, const v4f &qs) {
     const uint32_t lo = __builtin_amdgcn_perm((uint32_t)q8((float)v[1] * qs[1]), (uint32_t)q8((float)v[0] * qs[0]),
