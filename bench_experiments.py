@@ -5,7 +5,8 @@ bench.py: the planner evaluation in the manner of the paper's Table 1
 (--paper-grid), the LUT latency predictor of Eq. 1 and the layer-wise search
 of Alg. 1 on ViT-L (--predictor), the int8 chaining epilogue (--chaining),
 the per-shape roofline table (--shape-report), a DeiT-B layer captured in a
-HIP graph (--graph-layer) and the rocprofv3 summary writer
+HIP graph (--graph-layer), the schedule of calls without a plan on random
+shapes (--schedule-eval) and the rocprofv3 summary writer
 (--rocprof-summary).  Each writes its report under profiles/ when asked and
 prints one JSON line.
 """
@@ -1124,6 +1125,118 @@ def chain_sweep(torch, cfg, rounds, out_path, report, carried=False):
     return summary
 
 
+SCHEDULE_RANGES = {   # (m, n, k): lowest and highest, drawn evenly over the logarithm
+    "fitted range": ((64, 60000), (128, 4096), (128, 4096)),
+    "k above 4096": ((64, 20000), (128, 16384), (4112, 16384)),
+    "few tokens": ((1, 63), (128, 8192), (128, 8192)),
+    "many tokens": ((60001, 400000), (16, 1024), (32, 1024)),
+}
+
+
+def schedule_eval(torch, count, seed, report):
+    """The tile that calls without a plan run, against the planner's tile and
+    the best of all tiles, on random shapes: every tile in a HIP graph whose
+    calls take the next of two to eight sets of X and outputs (600 MB where
+    the shape allows), median of five replays, the lesser of two such passes."""
+    import math
+    import random
+
+    from paper_2607_12505_amd import nmprobe
+    rng = random.Random(seed)
+
+    def draw(lo, hi, step):
+        v = math.exp(rng.uniform(math.log(lo), math.log(hi)))
+        return max(-(-lo // step) * step, min(hi // step * step, int(round(v / step)) * step))
+
+    def replay_us(graph, launches):
+        graph.replay()
+        out = []
+        for _ in range(5):
+            e0, e1 = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            e0.record()
+            graph.replay()
+            e1.record()
+            e1.synchronize()
+            out.append(e0.elapsed_time(e1) * 1e3 / launches)
+        return sorted(out)[2]
+
+    def random_bytes(shape, dtype=torch.int8):
+        return torch.randint(-127, 128, shape, dtype=torch.int8, device="cuda").view(dtype)
+
+    res = {}
+    for name, (ms, ns, ks) in SCHEDULE_RANGES.items():
+        rows = []
+        while len(rows) < count:
+            m, n, k = draw(*ms, 1), draw(*ns, 4), draw(*ks, 16)
+            if m * n > 2 ** 27 or m * n * k > 2e11:
+                continue
+            N, M = rng.choice(((2, 4), (1, 4), (1, 8), (2, 8), (3, 8), (4, 8), (5, 8), (8, 8)))
+            mode = rng.choice((nmspmm.NM_OUT_I32, nmspmm.NM_OUT_F16, nmspmm.NM_OUT_I8,
+                               nmspmm.NM_OUT_I32 | nmspmm.NM_OUT_F16))
+            d = nmspmm.compress_size(n, k, N, M)
+            plan = nmspmm.spmm_plan(d, m, mode)
+            kind = nmspmm.expand_size(d)[0].kind if plan.expand else d.kind
+            chosen = nmprobe.schedule_tile(kind, m, n, k, mode, plan.tile)
+            # values and positions of any bytes: the kernels take the same time on them
+            w = nmspmm.DeviceWeight(random_bytes((d.vals_bytes,)), random_bytes((d.meta_bytes,), torch.uint8), d)
+            per_set = m * k + m * n * sum(b for b, o in ((4, nmspmm.NM_OUT_I32), (2, nmspmm.NM_OUT_F16),
+                                                         (1, nmspmm.NM_OUT_I8)) if mode & o)
+            sets, scale = [], torch.full((n,), 1e-4, device="cuda")
+            for _ in range(max(2, min(8, (600 << 20) // per_set + 1))):
+                o = {}
+                if mode & nmspmm.NM_OUT_I32:
+                    o["Y"] = torch.empty((m, n), dtype=torch.int32, device="cuda")
+                if mode & nmspmm.NM_OUT_F16:
+                    o.update(Yh=torch.empty((m, n), dtype=torch.float16, device="cuda"), scale=scale)
+                if mode & nmspmm.NM_OUT_I8:
+                    o.update(Yq=torch.empty((m, n), dtype=torch.int8, device="cuda"), qscale=scale)
+                sets.append((random_bytes((m, k)), o))
+            launches, graphs = max(8, 2 * len(sets)), {}
+            for tile in range(nmprobe.num_schedule_tiles()):
+                try:
+                    nmprobe.probe_spmm_tile(sets[0][0], w, tile, **sets[0][1])
+                except nmspmm.NmError:
+                    continue                      # not built for this kind
+                torch.cuda.synchronize()
+                graphs[tile] = torch.cuda.CUDAGraph()
+                with torch.cuda.graph(graphs[tile]):
+                    for i in range(launches):
+                        X, o = sets[i % len(sets)]
+                        nmprobe.probe_spmm_tile(X, w, tile, **o)
+            times = {t: replay_us(g, launches) for t, g in graphs.items()}
+            times = {t: min(times[t], replay_us(g, launches)) for t, g in graphs.items()}
+            rows.append((times[chosen] / times[plan.tile], times[chosen] / min(times.values()),
+                         times[plan.tile] / min(times.values())))
+            if len(rows) % 20 == 0:
+                log(f"{name}: {len(rows)} of {count}")
+            del sets, graphs
+            torch.cuda.empty_cache()
+        r = np.array(rows)
+        mean = np.exp(np.log(r).mean(axis=0))
+        res[name] = {"shapes": count, "chosen_over_planned": round(float(mean[0]), 3),
+                     "slower_than_planned_3pct": round(float((r[:, 0] > 1.03).mean()), 3),
+                     "slower_than_planned_8pct": round(float((r[:, 0] > 1.08).mean()), 3),
+                     "worst_over_planned": round(float(r[:, 0].max()), 2),
+                     "chosen_over_best": round(float(mean[1]), 3), "planned_over_best": round(float(mean[2]), 3)}
+    if report:
+        md = ["# Calls without a plan: the chosen tile on random shapes", "",
+              f"Command: `python3 bench_experiments.py --schedule-eval {count} --seed {seed} --report {report}` "
+              "(repository root).  Shapes drawn evenly over the logarithm of each size, every pattern and output, none "
+              "of them used to fit the estimate.  Every tile is timed in a HIP graph whose calls take the next of two to "
+              "eight sets of X and outputs (600 MB where the shape allows; the weight stays the same).  Averages are "
+              "geometric means of time ratios.", "",
+              "| range | m | n | k | shapes | chosen / planner's | >3 % slower | >8 % slower | worst | chosen / best | "
+              "planner's / best |", "|---|---|---|---|---:|---:|---:|---:|---:|---:|---:|"]
+        for name, v in res.items():
+            span = " | ".join(f"{lo}–{hi}" for lo, hi in SCHEDULE_RANGES[name])
+            md.append(f"| {name} | {span} | {v['shapes']} | {v['chosen_over_planned']:.3f} | "
+                      f"{100 * v['slower_than_planned_3pct']:.1f} % | {100 * v['slower_than_planned_8pct']:.1f} % | "
+                      f"{v['worst_over_planned']:.2f} | {v['chosen_over_best']:.3f} | {v['planned_over_best']:.3f} |")
+        with open(report, "w") as f:
+            f.write("\n".join(md) + "\n")
+    return res
+
+
 def main():
     ap = argparse.ArgumentParser(description=__doc__, formatter_class=argparse.RawDescriptionHelpFormatter)
     ap.add_argument("--sweep", type=str, default=None,
@@ -1159,6 +1272,9 @@ def main():
                     help="per-shape roofline of every workload GEMM (prints one JSON line; --report for markdown)")
     ap.add_argument("--chain-sweep", type=int, default=None, metavar="CFG",
                     help="tile and expansion candidates timed inside the steps of workload CFG (e.g. 4)")
+    ap.add_argument("--schedule-eval", type=int, default=None, metavar="COUNT",
+                    help="chosen, planned and best tile on COUNT random shapes per range (one JSON line)")
+    ap.add_argument("--seed", type=int, default=1, help="seed of --schedule-eval")
     ap.add_argument("--rounds", type=int, default=2, help="ABBA rounds per candidate of --chain-sweep")
     ap.add_argument("--cal", type=int, default=64, help="calibration configurations for --predictor")
     ap.add_argument("--test", type=int, default=32, help="random test configurations for --predictor")
@@ -1198,6 +1314,9 @@ def main():
         print(json.dumps({"predictor": predictor_experiment(torch, args.cal, args.test, args.report)}), flush=True)
     elif args.shape_report:
         print(json.dumps({"shape_report": shape_report(torch, args.report)}), flush=True)
+    elif args.schedule_eval:
+        print(json.dumps({"schedule_eval": schedule_eval(torch, args.schedule_eval, args.seed, args.report)}),
+              flush=True)
     elif args.graph_layer:
         print(json.dumps({"graph_layer": graph_layer(torch)}), flush=True)
     else:

@@ -286,17 +286,17 @@ nm_status make_plan(int kind, int m, int n, int k, int out_mode, nm_plan *plan) 
 // 64..60000, n and k 128..4096 with int32, fp16 and int8 outputs, and on the
 // linears of DeiT, Swin-B and ViT-L.
 //
-// Held out (2373 other shapes; every tile timed in graphs, each call on the
-// next of two to eight sets of buffers): over the fitted range the chosen tile
-// is 2.6 % from the best on average (the planner's 8.2 %) and takes 0.948 of
-// the planner's time; one shape in 14 loses more than 3 % to the planner's
-// tile, one in 38 more than 8 % (at most 17 %).  A switch is made for a promise
-// of 3 % there: asking for 6 or 10 % would lose more on average than those
-// shapes gain (0.952 and 0.960).  Reductions longer than any fitted one (k
-// above 4096, timed to 16384) are extrapolated, and the estimate errs more: at
-// 3 % one shape in 8 lost more than 3 % (m 2604, n 1416, k 6240, 2:8: 41.1 ->
-// 50.8 us; m 2458, n 1508, k 15120, 2:4: 90.5 -> 113.1), so a switch has to
-// promise 12 % there: one in 58, and 0.873 of the planner's time against 0.877.
+// Held out (bench_experiments.py --schedule-eval: every tile on 400 other
+// shapes per range): over the fitted range the chosen tile is 2.6 % from the
+// best on average (the planner's 8.9 %) and takes 0.942 of the planner's time;
+// one shape in 19 loses more than 3 % to the planner's tile, one in 50 more
+// than 8 % (at most 17 %).  A switch is made for a promise of 3 % there: on 1848
+// shapes that gave 0.948, asking for 6 or 10 % 0.952 and 0.960.  Reductions
+// longer than any fitted one are extrapolated, and the estimate errs more: on
+// 525 shapes with k to 16384, at 3 % one in 8 lost more than 3 % (m 2604,
+// n 1416, k 6240, 2:8: 41.1 -> 50.8 us; m 2458, n 1508, k 15120, 2:4: 90.5 ->
+// 113.1), so a switch has to promise 12 % there: one in 58, and 0.873 of the
+// planner's time against 0.877; on the 400 other shapes one in 57, and 0.848.
 constexpr int kFittedK = 4096;
 
 struct CostTerms {
